@@ -116,11 +116,10 @@ struct AsCfg {
   static constexpr int mx(int x, int y) { return x > y ? x : y; }
   static constexpr int oOm = 0;                                             // Omega block [p][D]
   static constexpr int oM = oOm + a16(FB * (D + PAD) * ES);                 // boundary M ([d][sigma(p)] or [p][d])
-  static constexpr int TPF = tr_pad<T, FB>(), TPD = tr_pad<T, D>();
-  // row pitches: chi and r are read transposed
-  static constexpr int CST = FB + TPF;
+  static constexpr int TPD = tr_pad<T, D>();
+  static constexpr int CST = FB + PAD;
   static constexpr int VST = DV + PAD;
-  static constexpr int RST = D + TPD;
+  static constexpr int RST = D + PAD;
   static constexpr int oChi = oM + a16(mx(DV * (FB + PAD), FB * (DV + PAD)) * ES);   // chi [j][sigma(p)]
   static constexpr int oV = oChi + a16(32 * CST * ES);                      // V [j][d]
   static constexpr int oQ = oV + a16(32 * VST * ES);                        // q rows of the chunk
@@ -129,8 +128,8 @@ struct AsCfg {
   static constexpr int oRj = oU + a16(32 * (DV + PAD) * ES);                // R_j of the chunk
   static constexpr int oRat = oRj + a16(32 * 4);                            // 2^(R_j - Rref) of the chunk
   static constexpr int oA = oRat + a16(32 * 4);                             // boundary a
-  static constexpr int oW = oA + a16(FB * 4);                               // per wave: dN (DV), s_c (32)
-  static constexpr int oOb = oW + a16(NW * (DV + 32) * 4);                 // Omega*log2 e, operand type (dz)
+  static constexpr int oW = oA + (sizeof(T) == 4 ? a16(FB * 4) : 0);        // per wave: dN of two rows (2 DV), s_c (32)
+  static constexpr int oOb = oW + a16(NW * (2 * DV + 32) * 4);             // Omega*log2 e, operand type (dz)
   static constexpr int BYTES0 = oOb + a16(FB * (D + TPD) * ES);
   static constexpr int RED = (NW / 2) * 32 * mx(DV, D) * 4;                 // end-of-sweep reduction
   static constexpr int BYTES = mx(BYTES0, RED);
@@ -479,6 +478,14 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_du(BwdArgs a) {
 //   dz_c = Omega^T dell_c - s_c z_c  ->  dr_c += dz_c (*) q_i,  dq_i += dz_c (*) r_c
 // dr stays in registers (regs <-> anchor, lanes <-> D); each row's dq over this
 // tile is complete in one wave and goes to slot (chunk of i) - (tile) of dq32.
+//
+// Bound by its per-item VALU and matrix-core work at two waves per SIMD (256
+// registers).  Of the 95 rows that see a tile at w = 64, 32 see only one
+// 16-anchor half of it; two of those share one item, 79 items instead of 95.
+// At d = m = 128, 2 x 16 heads of 16384 tokens the sweep went from 7.10 to
+// 6.40 ms, at d = 64, m = 128, 8 x 6 heads of 2048 tokens from 0.74 to 0.64.
+// The bodies keep no branch between the dr updates (a conditional store there
+// cost 64 register copies of dr per row).
 // ---------------------------------------------------------------------------
 template <typename T, int D, int DV, int M, int NA>
 __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
@@ -502,8 +509,8 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
   float* sRat = (float*)(smem + C::oRat);
 
   const int tid = threadIdx.x, l = tid & 63, col = l & 31, h = l >> 5, wv = uniform(tid >> 6);
-  float* sDN = (float*)(smem + C::oW) + wv * (DV + 32);
-  float* sSc = sDN + DV;
+  float* sDN = (float*)(smem + C::oW) + wv * (2 * DV + 32);
+  float* sSc = sDN + 2 * DV;
   const int2 gxy = xcd_grid_xy();
   const int kt = gxy.x, bh = gxy.y, hh = bh % a.H, n = a.n, nch = a.nch, fb = blockIdx.z;
   const int c0 = kt * 32, w = a.w;
@@ -551,6 +558,25 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
     //   dpsi = 2^(Rref - R_i) [M_b dA + dZ a_b + sum_{j <= i} 2^(R_j - Rref) chi_j (v_j . dA + dZ)]
     // and the row factor 2^(Rref - R_i) goes into dN and dZ once per row
     const float Rref = uniform(has_bnd ? Rexb : a.rj[seq + s0]);
+    // The rows of the chunk that see the tile, by what they see of it (rel = the
+    // chunk's offset from the tile, w the window): rows rel + t <= 15 only its
+    // low 16 anchors, rows rel + t >= w + 15 only its high 16, the rest any of
+    // them.  Two half-tile rows run as one item, anchors 0..15 of the item's 32
+    // slots for the first row, 16..31 for the second.
+    const int rel = s0 - c0;
+    const int tend = min(min(32, n - s0), w + 31 - rel);        // rows t < tend see the tile
+    const int tlo = rel == 0 ? min(16, tend) : 0;               // low half: [0, tlo)
+    const int thi = min(max(w + 15 - rel, tlo), tend);          // full: [tlo, thi), high half: [thi, tend)
+
+    constexpr int NG = (DV + 63) / 64;
+    auto load_g = [&](float (&g)[NG], int t) {
+      const size_t i = (size_t)min(s0 + t, n - 1);
+#pragma unroll
+      for (int e = 0; e < NG; ++e) g[e] = (e * 64 + l < DV) ? tof(gs[i * DV + e * 64 + l]) : 0.0f;
+    };
+    const int nlo = (tlo + 1) >> 1, nhi = (tend - thi + 1) >> 1;   // pairs of half-tile rows
+    const int tl = 2 * wv;                                         // this wave's low pair
+    float gA[NG], gB[NG];
     {
       // the chunk's global loads, each batch issued in full before its LDS
       // stores (float32 inputs: the state in two halves, the second with
@@ -581,8 +607,9 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
         sm.store(tid, put(0));
         if (has_bnd) sm.load(bst + (size_t)(fb * FB + FH) * DV, tid);
       }
-      if (tid < FB) sA[tid] = av;
-      if constexpr (sizeof(T) == 2) {
+      if constexpr (sizeof(T) == 4) {
+        if (tid < FB) sA[tid] = av;
+      } else {
         // bf16: a_b rides in the padding of M_b's row p as one more k-step of
         // the boundary product, (a_hi, a_hi, a_lo, 0, ...) against the row's
         // (dZ_hi, dZ_lo, dZ_hi, 0, ...): a_b dZ to about 16 bits
@@ -598,6 +625,10 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
       sv.load(vs, DV, s0, 0, n, tid);
       sq.load(qs, D, s0, 0, n, tid);
       const float rjv = (tid < 32) ? a.rj[seq + min(s0 + tid, n - 1)] : 0.0f;
+      // the upstream-gradient rows of the wave's pair (rows clamped)
+      const int tp = nlo > 0 ? tl : thi + 2 * wv;
+      load_g(gA, tp);
+      load_g(gB, tp + 1);
       if constexpr (sizeof(T) != 2) sm.store(tid, put(FH));
       sc.store(sChi, C::CST, s0, 0, n, tid);
       sv.store(sV, C::VST, s0, 0, n, tid);
@@ -610,62 +641,70 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
     }
     __syncthreads();
 
-    // upstream-gradient rows are fetched one row ahead
-    constexpr int NG = (DV + 63) / 64;
-    float gpre[NG];
-    auto load_g = [&](int t) {
-      const size_t i = (size_t)min(s0 + t, n - 1);
-#pragma unroll
-      for (int e = 0; e < NG; ++e) gpre[e] = (e * 64 + l < DV) ? tof(gs[i * DV + e * 64 + l]) : 0.0f;
-    };
-    load_g(wv);
-#pragma unroll 1
-    for (int t = wv; t < 32; t += NW) {
-      float gv[NG];
-#pragma unroll
-      for (int e = 0; e < NG; ++e) gv[e] = gpre[e];
-      if (t + NW < 32) load_g(t + NW);
-      const int i = s0 + t;
-      if (i >= n || i < c0 || i - c0 > w + 30) continue;
+    // half: -1 a full row tA; 0 / 1 the low / high half of rows tA and tB (tB < 0: none)
+    auto item = [&](const int tA, const int tB, const float (&gA)[NG], const float (&gB)[NG], auto half_c) {
+      constexpr int HALF = decltype(half_c)::value;
+      constexpr bool PACK = HALF >= 0;
       __builtin_amdgcn_iglp_opt(0);             // interleave the matrix-core and LDS streams
-      const float Li = uniform(a.stats[(seq + i) * 2]);
-      const float inv = uniform(a.rowstat[(seq + i) * 2]);
-      const float dZ = uniform(a.rowstat[(seq + i) * 2 + 1]);
-      const float Ri = uniform(sRj[t]);
-      const float sbr = uniform(fast_exp2(Rref - Ri));
+      // the lane number made opaque: the body's LDS addresses are formed in the
+      // body instead of being held in registers across all three
+      int l = lane_id();
+      asm volatile("" : "+v"(l));
+      const int col = l & 31, h = l >> 5;
+      const bool second = PACK && col >= 16;    // this lane's slot belongs to row tB
+      const bool okl = !(second && tB < 0);
+      const int tBc = tB < 0 ? tA : tB;
+      // row scalars: of the item's row, or of the lane's row
+      auto row_scalar = [](float x) { return PACK ? x : uniform(x); };
+      const int t = second ? tBc : tA;
+      const int i = s0 + t;
+      const int ac = PACK ? (col & 15) + 16 * (HALF > 0) : col;   // the lane's anchor within the tile
+      const float Li = row_scalar(a.stats[(seq + i) * 2]);
+      const float inv = row_scalar(a.rowstat[(seq + i) * 2]);
+      const float dZ = row_scalar(a.rowstat[(seq + i) * 2 + 1]);
+      const float Ri = row_scalar(sRj[t]);
+      const float sbr = row_scalar(fast_exp2(Rref - Ri));
       const float dZr = dZ * sbr;
       const float invr = inv * sbr;
+      if constexpr (PACK) {
+        const float invrB = rlane(invr, 16);
+        const float invrA = rlane(invr, 0);
 #pragma unroll
-      for (int e = 0; e < NG; ++e)
-        if (e * 64 + l < DV) sDN[e * 64 + l] = gv[e] * invr;
+        for (int e = 0; e < NG; ++e)
+          if (e * 64 + l < DV) {
+            sDN[e * 64 + l] = gA[e] * invrA;
+            sDN[DV + e * 64 + l] = gB[e] * invrB;
+          }
+      } else {
+#pragma unroll
+        for (int e = 0; e < NG; ++e)
+          if (e * 64 + l < DV) sDN[e * 64 + l] = gA[e] * invr;
+      }
+      const float* dnl = sDN + (second ? DV : 0);
       const T* qrow = sQ + t * (D + PAD);
-      float qD[D / 32];
-#pragma unroll
-      for (int Dt = 0; Dt < D / 32; ++Dt)
-        qD[Dt] = sizeof(T) == 2 ? (float)((const f16*)qrow)[Dt * 32 + col] : tof(qrow[Dt * 32 + col]);
       wave_lds_sync();
-      const int c = c0 + col;
-      const bool valid = (i - c >= 0) && (i - c < w);
+      const int c = c0 + ac;
+      const bool valid = okl && (i - c >= 0) && (i - c < w);
       // psi only scales dpsi here: f16 fragments (bf16 inputs)
       using PF = typename std::conditional<sizeof(T) == 2, f16x8, typename F::frag>::type;
       PF pf[FB / 32][F::CSTEPS];
-      query_features<T, D, FB, PF>(pf, qrow, sR + col * (C::RST), sOm, valid, Li);
+      query_features<T, D, FB, PF>(pf, qrow, sR + ac * (C::RST), sOm, valid, Li);
       // dA^T fragments: lanes <-> anchor, natural d order
-      const T* urow = sU + col * (DV + PAD);
+      const T* urow = sU + ac * (DV + PAD);
       typename F::frag daf[DV / F::KS];
 #pragma unroll
       for (int s = 0; s < DV / F::KS; ++s) {
         const int k0 = s * F::KS + h * F::KPL;
         if constexpr (sizeof(T) == 2) {
           const f16x8 uf = *(const f16x8*)((const f16*)urow + k0);
-          const f32x4 d0 = *(const f32x4*)(sDN + k0), d1 = *(const f32x4*)(sDN + k0 + 4);
+          const f32x4 d0 = *(const f32x4*)(dnl + k0), d1 = *(const f32x4*)(dnl + k0 + 4);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             daf[s][e] = (bf16)__builtin_fmaf((float)uf[e], d0[e], 0.0f);   // one mixed-precision FMA
             daf[s][4 + e] = (bf16)__builtin_fmaf((float)uf[4 + e], d1[e], 0.0f);
           }
         } else {
-          daf[s] = F::ld(urow, k0) * sDN[k0];
+          daf[s] = F::ld(urow, k0) * dnl[k0];
         }
       }
       // Q^T[j, c] = (v_j . dA_c + dZ_i) 2^(R_j - Rref), j <= i  (regs <-> j, lanes <-> anchor;
@@ -739,7 +778,8 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
       if (h == 0) sSc[col] = valid ? sc : 0.0f;
       wave_lds_sync();
       // dz[c, D] (regs <-> anchor, lanes <-> D)
-      float* dqo = a.dq32 + ((((size_t)fb * NS + (ch - kt)) * a.BH + bh) * n + i) * D;
+      float dqe = 0.0f;                         // the even slice's dq until the odd one's
+      float* dqs0 = a.dq32 + ((((size_t)fb * NS + (ch - kt)) * a.BH + bh) * n + s0) * D;
 #pragma unroll
       for (int Dt = 0; Dt < D / 32; ++Dt) {
         no_hoist();
@@ -749,34 +789,80 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
 #pragma unroll
           for (int sp = 0; sp < F::CSTEPS; ++sp)
             dz = F::mma(dlf[pt][sp], F::tld_crow(sOb, D + C::TPD, pt * 32, sp, Dt * 32), dz);
-        float rv[16];
+        // r of the registers' anchors (packed: slots 16..31 are the anchors of slots 0..15)
+        constexpr int NV = PACK ? 8 : 16, NSP = NV * F::CSTEPS / 16;
+        float rv[NV];
 #pragma unroll
-        for (int sp = 0; sp < F::CSTEPS; ++sp) {
+        for (int sp = 0; sp < NSP; ++sp) {
+          constexpr int rbase = HALF > 0 ? 16 : 0;
           if constexpr (sizeof(T) == 2) {
-            const f16x8 rf = tld_crow_f16((const f16*)sR, C::RST, 0, sp, Dt * 32);
+            const f16x8 rf = tld_crow_f16((const f16*)sR, C::RST, rbase, sp, Dt * 32);
 #pragma unroll
             for (int e = 0; e < 8; ++e) rv[8 * sp + e] = (float)rf[e];
           } else {
-            rv[sp] = F::tld_crow(sR, C::RST, 0, sp, Dt * 32);
+            rv[sp] = F::tld_crow(sR, C::RST, rbase, sp, Dt * 32);
           }
         }
-        const float qd = qD[Dt];
+        // q of the item's rows, lanes <-> D
+        float qd2[2];
+#pragma unroll
+        for (int x = 0; x < (PACK ? 2 : 1); ++x) {
+          const T* qx = sQ + (x == 0 ? tA : tBc) * (D + PAD) + Dt * 32 + col;
+          qd2[x] = sizeof(T) == 2 ? (float)*((const f16*)qx) : tof(*qx);
+        }
         const float* sch = sSc + 4 * h;
-        float dqs = 0.0f;
+        float dqs[2] = {0.0f, 0.0f};
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x4 s4 = *(const f32x4*)(sch + 8 * g);
+          const int x = PACK ? g >> 1 : 0;                     // the register's row
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const int v = 4 * g + e;
-            const float dzz = dz[v] - s4[e] * qd * rv[v];
-            dqs += dzz * rv[v];
-            dr[Dt][v] += dzz * qd;
+            const float qd = qd2[x], r1 = rv[v % NV];
+            const float dzz = dz[v] - s4[e] * qd * r1;
+            dqs[x] += dzz * r1;
+            dr[Dt][v % NV + (HALF > 0 ? 8 : 0)] += dzz * qd;
           }
         }
-        dqs = half_swap_add(dqs);
-        if (h == 0) dqo[Dt * 32 + col] = dqs;
+        // stored without a branch (which would split the body and cost a copy of
+        // dr): packed, half 0 has row tA's sum and half 1 row tB's; else half h
+        // has that of the D slice Dt + h
+        if constexpr (PACK) {
+          const float xA = half_swap_add(dqs[0]), xB = half_swap_add(dqs[1]);
+          const bool toA = h == 0 || tB < 0;
+          dqs0[(size_t)(toA ? tA : tBc) * D + Dt * 32 + col] = toA ? xA : xB;
+        } else if constexpr (D == 32) {
+          const float x = half_swap_add(dqs[0]);       // both halves store it
+          dqs0[(size_t)tA * D + col] = x;
+        } else {
+          const float x = half_swap_add(dqs[0]);
+          if (Dt % 2 == 0) dqe = x;
+          else dqs0[(size_t)tA * D + (Dt - 1) * 32 + l] = h == 0 ? dqe : x;
+        }
       }
+    };
+    // at most eight pairs of either kind: one per wave.  Upstream-gradient rows
+    // are fetched one row ahead, the first full row's before the pairs; the
+    // waves left idle by the pairs take the first full rows
+    const int tf0 = tlo + ((wv - nlo - nhi) & (NW - 1));
+    float gpre[NG];
+    load_g(gpre, tf0);
+    if (wv < nlo) item(tl, tl + 1 < tlo ? tl + 1 : -1, gA, gB, std::integral_constant<int, 0>{});
+    const int wh = (wv - nlo) & (NW - 1), th = thi + 2 * wh;
+    if (wh < nhi) {
+      if (nlo > 0) {                              // (narrow windows: the prefetched pair was a low one)
+        load_g(gA, th);
+        load_g(gB, th + 1);
+      }
+      item(th, th + 1 < tend ? th + 1 : -1, gA, gB, std::integral_constant<int, 1>{});
+    }
+#pragma unroll 1
+    for (int t = tf0; t < thi; t += NW) {
+#pragma unroll
+      for (int e = 0; e < NG; ++e) gA[e] = gpre[e];
+      if (t + NW < thi) load_g(gpre, t + NW);
+      item(t, -1, gA, gA, std::integral_constant<int, -1>{});
     }
   }
   reduce_waves<D / 32>(dr, (float*)smem, wv, NW);

@@ -113,6 +113,21 @@ def test_backward_wide_windows(D, m, w, n, dt):
     _run(Workload("wide_bwd", 1, 2, n, D, D, m, w, dt, "fwdbwd", seed=42))
 
 
+@pytest.mark.parametrize("D,m,n,w,dt", [
+    (64, 64, 79, 15, "bf16"),     # low and high half-tile rows in one chunk, odd counts
+    (64, 64, 95, 16, "bf16"),
+    (32, 32, 110, 17, "f32"),
+    (128, 128, 139, 33, "bf16"),  # high half-tile rows straddle two chunks
+    (128, 64, 141, 50, "bf16"),
+    (64, 128, 113, 64, "bf16"),   # the sequence ends inside a pair
+    (32, 64, 73, 2, "f32"),
+])
+def test_backward_half_tile_rows(D, m, n, w, dt):
+    """The dq/dr sweep packs two rows that see only one half of a 32-anchor
+    tile into one item: windows and lengths at the edges of that split."""
+    _run(Workload("half_bwd", 1, 2, n, D, D, m, w, dt, "fwdbwd", seed=47))
+
+
 @pytest.mark.parametrize("D,m,n,w,dt", [(128, 128, 250, 64, "bf16"), (64, 64, 200, 40, "f32")])
 def test_backward_tile_grid_multiple_of_8(D, m, n, w, dt):
     """Tiles x heads a multiple of eight (here 8 x 4 and 7 x 8): the sweeps
