@@ -293,8 +293,7 @@ int linsimp_fwd(const linsimp_dims* dims, const void* q, const void* k, const vo
   if ((rc = check_ws(s, false, workspace, workspace_bytes_))) return rc;
   Workspace ws;
   carve(s, workspace, false, &ws);
-  rc = launch_forward(s, q, k, v, r, u, omega, out, stats, nullptr, nullptr, nullptr, ws,
-                      (hipStream_t)stream);
+  rc = launch_forward(s, q, k, v, r, u, omega, out, stats, ws, (hipStream_t)stream);
   if (rc == LINSIMP_OK) record_states(workspace, s, k, v, omega);
   else drop_states(workspace);
   return rc;
@@ -347,9 +346,7 @@ int linsimp_prefill(const linsimp_dims* dims, const void* k, const void* v, cons
   Workspace ws;
   carve(s, workspace, false, &ws);
   drop_states(workspace);          // the prefill leaves no reusable forward states
-  rc = launch_forward(s, k, k, v, r, u, omega, nullptr, nullptr, M, a, rho, ws, (hipStream_t)stream);
-  if (rc) return rc;
-  return launch_ring_fill(s, r, u, ring_r, ring_u, pos, (hipStream_t)stream);
+  return launch_prefill(s, k, v, r, u, omega, M, a, rho, ring_r, ring_u, pos, ws, (hipStream_t)stream);
 }
 
 int linsimp_decode_step(int64_t S, int32_t H, int32_t D, int32_t Dv, int32_t m, int32_t w,
@@ -498,8 +495,7 @@ int linsimp_fwd_static(const linsimp_dims* dims, const void* q, const void* k, c
   if ((rc = current_scratch(&base))) return rc;
   Workspace ws;
   carve(s, base, false, &ws);
-  return launch_forward(s, q, k, v, r, u, omega, out, stats, nullptr, nullptr, nullptr, ws,
-                        (hipStream_t)stream);
+  return launch_forward(s, q, k, v, r, u, omega, out, stats, ws, (hipStream_t)stream);
 }
 
 // ---- full head (include/linsimp_head.h) ----
@@ -612,8 +608,7 @@ int linsimp_head_fwd(const linsimp_dims* dims, const linsimp_head_opts* opts, co
   carve(s, workspace, false, &ws);
   drop_states(workspace);
   if ((rc = launch_head_prenorm(s, q, k, r, tau, hs.qn, hs.kn, hs.rn, opts->norm_eps, st))) return rc;
-  if ((rc = launch_forward(s, hs.qn, hs.kn, v, hs.rn, u, omega, hs.ot, hs.stats, nullptr, nullptr,
-                           nullptr, ws, st)))
+  if ((rc = launch_forward(s, hs.qn, hs.kn, v, hs.rn, u, omega, hs.ot, hs.stats, ws, st)))
     return rc;
   // the core's states are those of the normalised keys in `saved`
   record_states(workspace, s, hs.kn, v, omega);

@@ -1556,7 +1556,7 @@ int launch_backward(const Shape& s, const void* q, const void* k, const void* v,
   // the forward's prefix states (boundary states and frames): recomputed,
   // unless the caller's workspace still holds them from the forward
   if (!reuse_states) {
-    int rc = launch_forward(s, q, k, v, r, u, omega, nullptr, nullptr, nullptr, nullptr, nullptr, ws, st);
+    int rc = launch_forward(s, q, k, v, r, u, omega, nullptr, nullptr, ws, st);
     if (rc) return rc;
   }
   BwdArgs a;

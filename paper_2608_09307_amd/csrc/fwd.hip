@@ -31,7 +31,6 @@ struct FwdArgs {
   void* omq; void* omk; void* omh;
   float* states; float* rho; float* rex;
   void* states16;     // [BH][nch][m][Dv] bf16 inputs: the boundary states' M in bf16; null for float32
-  float* final_M; float* final_a; float* final_rex;   // optional state after the last token
   float* part;                                        // [NFB][BH][n][Dv+2] when m > 128
   void* chi;          // [BH][n][m] key features 2^(lambda_j - R_j)/sqrt(m), p permuted in 16-blocks
   float* rj;          // [BH][n]    running key frame R_j (log2)
@@ -224,14 +223,7 @@ __global__ __launch_bounds__(256) void k_state_scan(FwdArgs a) {
       R = Rn;
     }
   }
-  if (a.final_M != nullptr && act) {
-    if (i4 < M * DV) *(f32x4*)(a.final_M + (size_t)bh * M * DV + i4) = run;
-    else *(f32x4*)(a.final_a + (size_t)bh * M + (i4 - M * DV)) = run;
-  }
-  if (writer) {
-    rx[nch] = R;
-    if (a.final_rex != nullptr) a.final_rex[bh] = R;
-  }
+  if (writer) rx[nch] = R;
 }
 
 // ---------------------------------------------------------------------------
@@ -312,165 +304,6 @@ __global__ __launch_bounds__(256) void k_keyfeat(FwdArgs a) {
     const int idx = l + 64 * it, r = idx / PPR, c = (idx % PPR) * VE;
     if (r < nrow) *(V*)(dst + (size_t)r * M + c) = xs[it];
   }
-}
-
-// ---------------------------------------------------------------------------
-// Prefill: the state after all n tokens of each (sequence, head), directly
-// (eq:Mstate, eq:astate summed over the whole prefix, Theorem 1).  One
-// workgroup per (sequence, head); wave wv owns features 32 wv .. 32 wv + 31 and
-// walks the chunks in order, keeping its rows of M and a in registers in the
-// running key frame R (log2): per chunk, the key log2-features (bf16 hi/lo
-// Omega, two MFMAs per k-step: the hi half of the wave's tile in registers,
-// the lo half of all tiles in LDS, so that two workgroups fit on a CU with
-// two waves per SIMD), the chunk maximum shared across the waves,
-// the frame update (M, a scaled by 2^(R - R')), then M += chi^T V on the
-// matrix cores.  The chunk's k rows and V^T are staged in LDS one chunk ahead,
-// from registers loaded two chunks ahead.
-// Nothing but the final state is written (the chunked forward materialises
-// every chunk's contribution instead).  bf16 inputs, m <= 128.
-// ---------------------------------------------------------------------------
-template <int D, int DV, int M>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_prefill_state(FwdArgs a) {
-  using T = bf16;
-  using F = MF<T>;
-  constexpr int PAD = F::PAD, PT = M / 32;
-  static_assert(PT <= 4, "one feature tile per wave");
-  __shared__ __align__(16) T sK[2][32][D + PAD];
-  __shared__ __align__(16) T sOl[M][D + PAD];
-  __shared__ __align__(16) T sVt[2][DV][32 + PAD];
-  __shared__ __align__(16) float snk[4][32];
-  __shared__ float smx[4];
-  const int tid = threadIdx.x, l = tid & 63, col = l & 31, h = l >> 5, wv = uniform(tid >> 6);
-  const int bh = blockIdx.x, hh = bh % a.H, n = a.n, nch = a.nch;
-  const bool owner = wv < PT;
-  const size_t seq = (size_t)bh * n;
-  const T* ks = (const T*)a.k + seq * D;
-  const T* vs = (const T*)a.v + seq * DV;
-  const T* omk_h = (const T*)a.omk + (size_t)hh * 2 * M * D;
-  // hi half of this wave's Omega tile: B operands, lanes <-> feature p
-  typename F::frag oh[D / F::KS];
-#pragma unroll
-  for (int s = 0; s < D / F::KS; ++s) oh[s] = *(const typename F::frag*)(omk_h + bank_frag<T, D>(owner ? wv : 0, s, l));
-  {
-    // the lo half into LDS rows: fragment f of the bank goes to row 32 pt + col,
-    // columns s KS + h KPL onwards (every load issued before the first store)
-    constexpr int NS = D / F::KS, NF = (M / 32) * NS * 64, IT = (NF + 255) / 256;
-    static_assert(NF * F::KPL == M * D, "one fragment per lane, k-step and tile");
-    typename F::frag xs[IT];
-#pragma unroll
-    for (int it = 0; it < IT; ++it)
-      xs[it] = *(const typename F::frag*)(omk_h + (size_t)M * D + (size_t)min(tid + 256 * it, NF - 1) * F::KPL);
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int f = tid + 256 * it;
-      if (NF % 256 != 0 && f >= NF) continue;
-      const int ln = f & 63, s = (f >> 6) % NS, pt = (f >> 6) / NS;
-      *(typename F::frag*)&sOl[pt * 32 + (ln & 31)][s * F::KS + (ln >> 5) * F::KPL] = xs[it];
-    }
-  }
-  const T* olrow = &sOl[(owner ? wv : 0) * 32 + col][0];
-  f32x16 Macc[DV / 32];
-#pragma unroll
-  for (int dt = 0; dt < DV / 32; ++dt) Macc[dt] = zero16();
-  float apart = 0.0f;                          // sum over this lane's tokens of chi_p, p = 32 wv + col
-  float R = kNegInf;
-  const float rs = rsqrtf((float)M);
-
-  StageRows<T, 32, D, 256> sk;
-  StageRowsT<T, 32, DV, 256> sv;
-  auto stage_store = [&](int b, int buf) {
-    sk.store(&sK[buf][0][0], D + PAD, b * 32, 0, n, tid);
-    sv.store(b * 32, 0, n, tid, [&](int jj, int d0, const typename StageRowsT<T, 32, DV, 256>::V4& x) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sVt[buf][d0 + e][F::sigma(jj)] = x[e];
-    });
-  };
-  // chunk b + 1's rows are loaded while chunk b is folded in, and chunk b + 2's
-  // as soon as chunk b + 1 is in LDS: every load has about one chunk's work to land
-  sk.load(ks, D, 0, 0, n, tid);
-  sv.load(vs, DV, 0, 0, n, tid);
-  stage_store(0, 0);
-  sk.load(ks, D, 32, 0, n, tid);
-  sv.load(vs, DV, 32, 0, n, tid);
-
-#pragma unroll 1
-  for (int b = 0; b < nch; ++b) {
-    const int cur = b & 1;
-    __syncthreads();                           // chunk b staged; the other buffer is free
-    // key log2-features of the tile: regs <-> token crow(v, h), lanes <-> p
-    f32x16 acc = zero16();
-    float mx = kNegInf;
-    if (owner) {
-      // two independent accumulation chains (hi, lo), summed at the end
-      f32x16 part[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) part[i] = zero16();
-      float nkp = 0.0f;
-      const T* krow = &sK[cur][col][0];
-#pragma unroll
-      for (int s = 0; s < D / F::KS; ++s) {
-        const typename F::frag kf = F::ld(krow, s * F::KS + h * F::KPL);
-#pragma unroll
-        for (int e = 0; e < F::KPL; ++e) { const float x = fel(kf, e); nkp += x * x; }
-        part[0] = F::mma(kf, oh[s], part[0]);
-        part[1] = F::mma(kf, F::ld(olrow, s * F::KS + h * F::KPL), part[1]);
-      }
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[v] = part[0][v] + part[1][v];
-      const float nk = half_swap_add(nkp);     // |k|^2 of token col
-      if (h == 0) snk[wv][col] = nk;
-      wave_lds_sync();
-      float nkt[16];
-      crow_vals(snk[wv], nkt);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float x = acc[v] - 0.5f * kLog2e * nkt[v];
-        acc[v] = (b * 32 + crow(v, h) < n) ? x : kNegInf;
-        mx = fmaxf(mx, acc[v]);
-      }
-      mx = wave_max(mx);
-    }
-    if (l == 0) smx[wv] = mx;
-    if (b + 1 < nch) {
-      stage_store(b + 1, cur ^ 1);
-      sk.load(ks, D, (b + 2) * 32, 0, n, tid);
-      sv.load(vs, DV, (b + 2) * 32, 0, n, tid);
-    }
-    __syncthreads();
-    const float cm = fmaxf(fmaxf(smx[0], smx[1]), fmaxf(smx[2], smx[3]));
-    const float Rn = fmaxf(R, cm);
-    if (owner) {
-      const float sa = fast_exp2(R - Rn);      // 0 while the state is empty
-      if (sa != 1.0f) {
-#pragma unroll
-        for (int dt = 0; dt < DV / 32; ++dt) Macc[dt] *= sa;
-        apart *= sa;
-      }
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float c = fast_exp2(acc[v] - Rn) * rs;
-        acc[v] = c;
-        apart += c;
-      }
-#pragma unroll
-      for (int dt = 0; dt < DV / 32; ++dt)
-#pragma unroll
-        for (int sp = 0; sp < F::CSTEPS; ++sp)
-          Macc[dt] = F::mma(F::cfrag(acc, sp), F::ldc(&sVt[cur][dt * 32 + col][0], 0, sp, h), Macc[dt]);
-    }
-    R = Rn;
-  }
-  // M rows p = 32 wv + crow(v, h) (lanes <-> d), a[p], the frame
-  if (owner) {
-    float* Mo = a.final_M + (size_t)bh * M * DV;
-#pragma unroll
-    for (int dt = 0; dt < DV / 32; ++dt)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) Mo[(size_t)(wv * 32 + crow(v, h)) * DV + dt * 32 + col] = Macc[dt][v];
-    const float at = half_swap_add(apart);
-    if (h == 0) a.final_a[(size_t)bh * M + wv * 32 + col] = at;
-  }
-  if (tid == 0) a.final_rex[bh] = R;
 }
 
 // ---------------------------------------------------------------------------
@@ -560,15 +393,7 @@ __global__ __launch_bounds__(64) void k_state_scan_mma(FwdArgs a) {
 #pragma unroll
   for (int e = 0; e < PF; ++e)
     if (b0 + e < nch) step(b0 + e, e);
-  if (a.final_M != nullptr) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) a.final_M[((size_t)bh * M + p0 + crow(v, h)) * DV + d0 + col] = run[v];
-    if (aw) a.final_a[(size_t)bh * M + p0 + col] = runa;
-  }
-  if (writer) {
-    rx[nch] = R;
-    if (a.final_rex != nullptr) a.final_rex[bh] = R;
-  }
+  if (writer) rx[nch] = R;
 }
 
 // ---------------------------------------------------------------------------
@@ -970,18 +795,6 @@ static int run_fwd(const Shape& s, FwdArgs a, hipStream_t st) {
     ProfScope ps("prep_omega", st);
     k_prep_omega<T><<<(tot + 255) / 256, 256, 0, st>>>(a.omega, (T*)a.omq, (T*)a.omk, (f16*)a.omh, (int)s.H, M * D, D);
   }
-  if constexpr (sizeof(T) == 2 && M <= 128) {
-    if (a.out == nullptr && a.final_M != nullptr) {   // prefill: the final state only
-      { ProfScope ps("prefill_state", st);
-      k_prefill_state<D, DV, M><<<BH, 256, 0, st>>>(a); }
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) {
-        set_error("prefill launch failed: %s", hipGetErrorString(e));
-        return -4;
-      }
-      return 0;
-    }
-  }
   { ProfScope ps("chunk_state", st);
   k_chunk_state<T, D, DV, M><<<dim3((nch + 3) / 4, BH), 256, 0, st>>>(a); }
   if constexpr (sizeof(T) == 2) {
@@ -993,10 +806,8 @@ static int run_fwd(const Shape& s, FwdArgs a, hipStream_t st) {
     ProfScope ps("state_scan", st);
     k_state_scan<M, DV><<<dim3((S / 4 + 255) / 256, BH), 256, 0, st>>>(a);
   }
-  if (a.out != nullptr || a.final_M == nullptr) {      // not for a prefill
-    ProfScope ps("keyfeat", st);
-    k_keyfeat<T, D, M><<<dim3((nch + 3) / 4, BH), 256, 0, st>>>(a);
-  }
+  { ProfScope ps("keyfeat", st);
+  k_keyfeat<T, D, M><<<dim3((nch + 3) / 4, BH), 256, 0, st>>>(a); }
   if (a.out != nullptr) {
     constexpr int NFB = RCfg<T, D, DV, M, NW, NA>::NFB;
     { ProfScope ps("fwd_readout", st);
@@ -1010,68 +821,6 @@ static int run_fwd(const Shape& s, FwdArgs a, hipStream_t st) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     set_error("forward launch failed: %s", hipGetErrorString(e));
-    return -4;
-  }
-  return 0;
-}
-
-// Prefill ring: slot j mod w holds token j of the last min(n, w) tokens; the
-// slots no token reaches (n < w) are zero.  16-byte pieces of the rows, every
-// piece of a batch loaded (row index clamped) before the first is stored.
-template <typename T>
-__global__ __launch_bounds__(256) void k_ring_fill(const T* __restrict__ r, const T* __restrict__ u,
-                                                   T* __restrict__ rr, T* __restrict__ ru,
-                                                   int64_t* __restrict__ pos, int H, int n, int w,
-                                                   int D, int DV) {
-  constexpr int VE = 16 / (int)sizeof(T), NB = 8;
-  typedef T V __attribute__((ext_vector_type(VE)));
-  const int bh = blockIdx.x;
-  const int pr = D / VE, pw = pr + DV / VE, total = w * pw;
-  // the newest token j <= n - 1 with j mod w == slot (negative: none)
-  auto token = [&](int slot) { return (n - 1) - (((n - 1 - slot) % w + w) % w); };
-  for (int base = 0; base < total; base += 256 * NB) {
-    V x[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int idx = min(base + (int)threadIdx.x + 256 * i, total - 1);
-      const int slot = idx / pw, c = idx % pw;
-      const size_t j = (size_t)max(token(slot), 0);
-      const T* src = c < pr ? r + ((size_t)bh * n + j) * D + c * VE : u + ((size_t)bh * n + j) * DV + (c - pr) * VE;
-      x[i] = *(const V*)src;
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int idx = base + (int)threadIdx.x + 256 * i;
-      if (idx >= total) continue;
-      const int slot = idx / pw, c = idx % pw;
-      const bool ok = token(slot) >= 0;
-      V y;
-#pragma unroll
-      for (int e = 0; e < VE; ++e) y[e] = ok ? x[i][e] : (T)0.0f;
-      T* dst = c < pr ? rr + ((size_t)bh * w + slot) * D + c * VE : ru + ((size_t)bh * w + slot) * DV + (c - pr) * VE;
-      *(V*)dst = y;
-    }
-  }
-  if (threadIdx.x == 0 && bh % H == 0) pos[bh / H] = n;
-}
-
-int launch_ring_fill(const Shape& s, const void* r, const void* u, void* ring_r, void* ring_u,
-                     int64_t* pos, hipStream_t st) {
-  const int BH = (int)s.BH();
-  const int es = s.dtype == 1 ? 2 : 4;
-  if ((s.D * es) % 16 != 0 || (s.Dv * es) % 16 != 0) {
-    set_error("ring fill: rows of %d and %d elements are not whole 16-byte pieces", s.D, s.Dv);
-    return -2;
-  }
-  if (s.dtype == 1)
-    k_ring_fill<bf16><<<BH, 256, 0, st>>>((const bf16*)r, (const bf16*)u, (bf16*)ring_r, (bf16*)ring_u,
-                                          pos, (int)s.H, (int)s.n, s.w, s.D, s.Dv);
-  else
-    k_ring_fill<float><<<BH, 256, 0, st>>>((const float*)r, (const float*)u, (float*)ring_r,
-                                           (float*)ring_u, pos, (int)s.H, (int)s.n, s.w, s.D, s.Dv);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) {
-    set_error("ring fill launch failed: %s", hipGetErrorString(e));
     return -4;
   }
   return 0;
@@ -1100,13 +849,12 @@ bool fwd_combo_supported(int dtype, int D, int Dv, int m) {
 }
 
 int launch_forward(const Shape& s, const void* q, const void* k, const void* v, const void* r,
-                   const void* u, const float* omega, void* out, float* stats, float* final_M,
-                   float* final_a, float* final_rex, const Workspace& ws, hipStream_t st) {
+                   const void* u, const float* omega, void* out, float* stats, const Workspace& ws,
+                   hipStream_t st) {
   FwdArgs a;
   a.q = q; a.k = k; a.v = v; a.r = r; a.u = u; a.omega = omega;
   a.out = out; a.stats = stats;
   a.omq = ws.omq; a.omk = ws.omk; a.omh = ws.omh; a.states = ws.states; a.states16 = ws.states16; a.rho = ws.rho; a.rex = ws.rex;
-  a.final_M = final_M; a.final_a = final_a; a.final_rex = final_rex;
   a.H = (int)s.H; a.n = (int)s.n; a.w = s.w; a.nch = (int)s.nch(); a.BH = (int)s.BH(); a.eps = s.eps;
   a.part = ws.part;
   a.chi = ws.chi; a.rj = ws.rj;

@@ -65,12 +65,12 @@ void carve(const Shape& s, void* base, bool backward, Workspace* ws);
 
 // Returns 0 on success, negative linsimp status otherwise (message via set_error).
 int launch_forward(const Shape& s, const void* q, const void* k, const void* v, const void* r,
-                   const void* u, const float* omega, void* out, float* stats,
-                   float* final_M, float* final_a, float* final_rex, const Workspace& ws,
+                   const void* u, const float* omega, void* out, float* stats, const Workspace& ws,
                    hipStream_t st);
 bool fwd_combo_supported(int dtype, int D, int Dv, int m);
-int launch_ring_fill(const Shape& s, const void* r, const void* u, void* ring_r, void* ring_u,
-                     int64_t* pos, hipStream_t st);
+int launch_prefill(const Shape& s, const void* k, const void* v, const void* r, const void* u,
+                   const float* omega, float* M, float* a, float* rho, void* ring_r, void* ring_u,
+                   int64_t* pos, const Workspace& ws, hipStream_t st);
 
 int launch_backward(const Shape& s, const void* q, const void* k, const void* v, const void* r,
                     const void* u, const float* omega, const void* out, const float* stats,

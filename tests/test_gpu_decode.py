@@ -241,3 +241,40 @@ def test_decode_chunk_matches_steps_and_forward(dtype, D, m, w, P, T):
     print("      max rel_l2 over heads", max(errs), "row max", max(rows), flush=True)
     assert max(errs) < TOL[dtype]
     assert max(rows) <= ROW_TOL[dtype]
+
+
+@pytest.mark.parametrize("D,m,n,w,S,H,dt", [
+    (128, 128, 1, 64, 1, 2, "bf16"),      # one token: one partial chunk
+    (128, 128, 1185, 64, 1, 2, "bf16"),   # segments of several chunks, the last one short and ragged
+    (128, 256, 650, 20, 2, 1, "bf16"),    # eight waves
+    (128, 64, 2048, 100, 1, 1, "bf16"),   # whole chunks
+    (64, 128, 95, 33, 3, 2, "bf16"),
+    (64, 64, 1025, 64, 1, 3, "bf16"),     # one token in the last chunk
+    (32, 32, 40, 64, 2, 2, "bf16"),       # shorter than the window
+    (64, 64, 777, 96, 1, 2, "f32"),
+    (32, 64, 1000, 64, 2, 1, "f32"),
+    (64, 32, 33, 5, 1, 1, "f32"),
+    (32, 32, 513, 128, 1, 1, "f32"),
+])
+def test_prefill_state(D, m, n, w, S, H, dt):
+    """The prefilled state of every (sequence, head) against the oracle: M and a
+    brought to the oracle's frame, the rings exactly, the largest key feature at
+    scale 1/sqrt(m) in the returned frame (boosted keys in some chunks)."""
+    wl = Workload("prefill", S, H, n, D, D, m, w, dt, "fwd", seed=61, boost_frac=0.3, boost=2.0)
+    x = make_inputs(wl, device=DEV)
+    st = L.prefill(x["k"], x["v"], x["r"], x["u"], x["omega"], w)
+    torch.cuda.synchronize()
+    assert st["pos"].tolist() == [n] * S
+    # bf16: the features enter M rounded once (2^-9 each, averaging over tokens);
+    # a sums them in float32, from log-features good to 2^-16 of about 2^6
+    tol = {"f32": (1e-5, 1e-5), "bf16": (5e-3, 1e-3)}[dt]
+    for s in range(S):
+        for h in range(H):
+            ref = O.prefill_state(*(f64(x[c][s, h]) for c in "kvru"), f64(x["omega"][h]), w)
+            scale = 2.0 ** float(st["rho"][s, h].double())
+            assert rel_l2(f64(st["M"][s, h]) * scale, ref["M"]) <= tol[0]
+            assert rel_l2(f64(st["a"][s, h]) * scale, ref["a"]) <= tol[1]
+            lam = O.log_features(f64(x["k"][s, h]), f64(x["omega"][h])).max() / np.log(2.0)
+            assert abs(float(st["rho"][s, h]) - lam) <= 1e-3
+            assert np.array_equal(f64(st["ring_r"][s, h]), ref["ring_r"])
+            assert np.array_equal(f64(st["ring_u"][s, h]), ref["ring_u"])
