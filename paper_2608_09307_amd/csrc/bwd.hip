@@ -50,7 +50,7 @@ struct BwdArgs {
   const float* states;
   const void* states16;
   const float* rex;
-  float* gst;       // [BH][nch][M*DV + M]  GB_b, then Ghat_b
+  float* gst;       // [BH][nseg][M*DV + M] GB of each segment, then Ghat
   float* dchi;      // [BH][n][M]           intra-chunk key-feature gradient
   float* dvin;      // [NFB][BH][n][DV]     intra-chunk value gradient
   float* du32;      // [NFB][BH][n][DV]     per feature block (NFB > 1)
@@ -60,6 +60,7 @@ struct BwdArgs {
   float* rj;        // [BH][n]              running key frame R_j
   float* rowstat;   // [BH][n][2]: 1/(Z+eps), dZ
   int H, n, w, nch, BH;
+  int cpw, nseg;    // chunks per segment of the state sweep, segments per sequence
   float eps;
 };
 
@@ -650,6 +651,7 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
       // body instead of being held in registers across all three
       int l = lane_id();
       asm volatile("" : "+v"(l));
+      l &= 63;                                  // (its range, which the compiler no longer knows)
       const int col = l & 31, h = l >> 5;
       const bool second = PACK && col >= 16;    // this lane's slot belongs to row tB
       const bool okl = !(second && tB < 0);
@@ -905,13 +907,15 @@ __global__ __launch_bounds__(256) void k_bwd_final_dq(const float* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// k_bwd_state: state sweep of one chunk b, one wave per 32-feature tile.
+// k_bwd_state: state sweep of a segment of chunks, from its last chunk to its
+// first, one wave per 32-feature tile.
 // With dM^(i)[p, d] = sum_c psi_icp dA_ic[d] and da^(i)[p] = dZ_i sum_c psi_icp,
 // the rows are walked in reverse with the running (frame R_t) matrices
 //   F_t = dM^(t) + 2^(R_t - R_{t+1}) F_{t+1},   f_t likewise from da,
-// i.e. F_t = sum_{i >= t in the chunk} 2^(R_t - R_i) dM^(i).  They give
+// i.e. F_t = sum_{i >= t in the segment} 2^(R_t - R_i) dM^(i).  They give
 //   intra dchi_t = F_t v_t + f_t      intra dv_t = F_t^T chi_t
-//   GB_b = sum_i sb_i dM^(i) = 2^(Rex_b - R_s0) F_s0,   gb_b = 2^(Rex_b - R_s0) f_s0.
+//   GB = sum_i sb_i dM^(i) = 2^(Rex - R_s0) F_s0,   gb = 2^(Rex - R_s0) f_s0
+// (s0 the segment's first row, Rex the frame of the state before it).
 // The query features are formed with the (row, anchor) pair in registers
 // (lanes <-> feature p): L[c, p] = sum_D r_c[D] (q_i[D] Omega[p, D]), so the
 // wave's Omega tile is scaled by q_i once per row and multiplies the anchors'
@@ -999,10 +1003,8 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
   const int tid = threadIdx.x, l = tid & 63, col = l & 31, h = l >> 5, wv = uniform(tid >> 6);
   T* sQ = (T*)(smem + C::oQ) + wv * D;
   const int2 gxy = xcd_grid_xy();
-  const int cb = gxy.x, bh = gxy.y, hh = bh % a.H, n = a.n, nch = a.nch, fb = blockIdx.z;
-  const int s0 = cb * 32;
-  const int wb = s0 - (AW - 1);                // window row 0 = anchor s0 - (AW - 1)
-  const int tlast = min(31, n - 1 - s0);
+  const int sg = gxy.x, bh = gxy.y, hh = bh % a.H, n = a.n, nch = a.nch, fb = blockIdx.z;
+  const int cbf = sg * a.cpw, cbl = min(cbf + a.cpw, nch) - 1;   // first and last chunk of the segment
   const size_t seq = (size_t)bh * n;
   const T* qs = (const T*)a.q + seq * D;
   const T* vs = (const T*)a.v + seq * DV;
@@ -1010,10 +1012,26 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
   const T* us = (const T*)a.u + seq * DV;
   const T* gs = (const T*)a.dout + seq * DV;
   const T* omq_h = (const T*)a.omq + (size_t)hh * M * D;
-  const float Rexb = a.rex[(size_t)bh * (nch + 1) + cb];
   const int w = a.w;
   const int pw = fb * FB + wv * 32;            // first feature of this wave's tile
 
+  f32x16 Fm[DV / 32];
+#pragma unroll
+  for (int dt = 0; dt < DV / 32; ++dt) Fm[dt] = zero16();
+  float fpart = 0.0f;                          // f[p = col], partial over this half's anchors
+  float Rnext = 0.0f;                          // R of the first row of the chunk after this one
+
+#pragma unroll 1
+  for (int cb = cbl; cb >= cbf; --cb) {
+  // the thread number made opaque: the chunk's staging and LDS addresses are
+  // formed in the chunk instead of being held in registers across chunks
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  tid &= NT - 1;                               // (its range, which the compiler no longer knows)
+  const int l = tid & 63, col = l & 31, h = l >> 5;
+  const int s0 = cb * 32;
+  const int wb = s0 - (AW - 1);                // window row 0 = anchor s0 - (AW - 1)
+  const int tlast = min(31, n - 1 - s0);
   {
     // every global load of the window first, then the LDS stores
     StageRows<T, 32 * C::NT32, D, NT> sr;
@@ -1078,7 +1096,7 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
       }
     }
   }
-  // this wave's Omega tile (log2e-scaled) as B operands, resident in registers
+  // this wave's Omega tile (log2e-scaled) as B operands, in registers
   // (bf16 inputs: f16 copies of Omega*log2 e, q and r; the logits use the f16 matrix cores)
   using OF = typename std::conditional<sizeof(T) == 2, f16x8, float>::type;
   OF omf[D / F::KS];
@@ -1092,11 +1110,6 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
     }
   }
   __syncthreads();
-
-  f32x16 Fm[DV / 32];
-#pragma unroll
-  for (int dt = 0; dt < DV / 32; ++dt) Fm[dt] = zero16();
-  float fpart = 0.0f;                          // f[p = col], partial over this half's anchors
 
   // the rows' q, dout, v and statistics are fetched one row ahead
   constexpr int QE = (D + 63) / 64;
@@ -1119,7 +1132,7 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
   for (int t = tlast; t >= 0; --t) {
     const float inv = uniform(invn);
     const float dZ = uniform(dZn);
-    const float fr = uniform(t < tlast ? fast_exp2(sRj[t] - sRj[t + 1]) : 1.0f);
+    const float fr = uniform(t < tlast ? fast_exp2(sRj[t] - sRj[t + 1]) : cb < cbl ? fast_exp2(sRj[t] - Rnext) : 1.0f);
 #pragma unroll
     for (int e = 0; e < QE; ++e)
       if (e * 64 + l < D) {
@@ -1241,10 +1254,14 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
       __syncthreads();
     }
   }
-  // ---- GB (frame Rex_b) and gb ----
+  Rnext = uniform(sRj[0]);
+  __syncthreads();                             // the chunk's rows are done with LDS
+  }
+  // ---- GB (frame Rex of the segment's first chunk) and gb ----
   constexpr int S = M * DV + M;
-  float* g = a.gst + ((size_t)bh * nch + cb) * S;
-  const float fac = fast_exp2(Rexb - sRj[0]);  // 0 for the first chunk (Rex_0 = -inf)
+  float* g = a.gst + ((size_t)bh * a.nseg + sg) * S;
+  const float Rexb = a.rex[(size_t)bh * (nch + 1) + cbf];
+  const float fac = fast_exp2(Rexb - Rnext);   // 0 for the first chunk (Rex_0 = -inf)
 #pragma unroll
   for (int dt = 0; dt < DV / 32; ++dt)
 #pragma unroll
@@ -1254,9 +1271,10 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// reverse exclusive scan:  Ghat_b = GB_{b+1} + 2^(Rex_{b+1} - Rex_{b+2}) Ghat_{b+1},
-// Ghat_{nch-1} = 0  (frame of Ghat_b: Rex_{b+1}, the running key max at the end
-// of chunk b).  In place, element-parallel, sequential over chunks.
+// reverse exclusive scan over the segments (Rex_b here the frame before segment
+// b):  Ghat_b = GB_{b+1} + 2^(Rex_{b+1} - Rex_{b+2}) Ghat_{b+1},  Ghat_last = 0
+// (frame of Ghat_b: Rex_{b+1}, the running key max at the end of segment b).
+// In place, element-parallel, sequential over segments.
 // ---------------------------------------------------------------------------
 template <int S>
 __global__ __launch_bounds__(256) void k_bwd_revscan(BwdArgs a) {
@@ -1264,11 +1282,11 @@ __global__ __launch_bounds__(256) void k_bwd_revscan(BwdArgs a) {
   const int bh = blockIdx.y;
   const int i4 = (blockIdx.x * 256 + threadIdx.x) * 4;
   if (i4 >= S) return;
-  const int nch = a.nch;
-  float* g = a.gst + (size_t)bh * nch * S;
-  const float* rx = a.rex + (size_t)bh * (nch + 1);
+  const int nseg = a.nseg;
+  float* g = a.gst + (size_t)bh * nseg * S;
+  const float* rx = a.rex + (size_t)bh * (a.nch + 1);
   f32x4 run = {0.f, 0.f, 0.f, 0.f};
-  for (int b1 = nch - 1; b1 >= 0; b1 -= PF) {
+  for (int b1 = nseg - 1; b1 >= 0; b1 -= PF) {
     f32x4 x[PF];
 #pragma unroll
     for (int e = 0; e < PF; ++e) {
@@ -1280,14 +1298,15 @@ __global__ __launch_bounds__(256) void k_bwd_revscan(BwdArgs a) {
       int b = b1 - e;
       if (b < 0) break;
       *(f32x4*)(g + (size_t)b * S + i4) = run;           // Ghat_b
-      const float f = fast_exp2(rx[b] - rx[b + 1]);       // 0 for b = 0 (Rex_0 = -inf)
+      const float f = fast_exp2(rx[b * a.cpw] - rx[min((b + 1) * a.cpw, a.nch)]);   // 0 for b = 0 (Rex_0 = -inf)
       run = x[e] + run * f;                               // Ghat_{b-1}
     }
   }
 }
 
 // ---------------------------------------------------------------------------
-// key side, per chunk b and token j (frame of the boundary gradient: Rex_{b+1}):
+// key side, per segment b and token j (frame of its boundary gradient: Rex_{b+1};
+// dchi_intra and dv_intra hold the rows i >= j of the segment):
 //   dchi_j = 2^(R_j - Rex_{b+1}) (Ghat_b v_j + ghat_b) + dchi_intra_j
 //   dv_j   = 2^(R_j - Rex_{b+1}) Ghat_b^T chi_j + dv_intra_j
 //   dlambda = dchi (*) chi;  dk_j = Omega^T dlambda_j - (sum_p dlambda_jp) k_j
@@ -1342,8 +1361,9 @@ __global__ __launch_bounds__(512) void k_bwd_keys(BwdArgs a, int nfb) {
   T* sDL = (T*)(smem + C::oDL) + cw * 32 * (M + PAD);
   T* sCE = (T*)(smem + C::oCE) + cw * 32 * (M + PAD);
   float* sSk = (float*)(smem + C::oSk) + cw * WPC * 32;
-  const int bh = blockIdx.y, hh = bh % a.H, n = a.n, nch = a.nch;
-  const int cb = blockIdx.x * C::CPB + cw;
+  const int2 gxy = xcd_grid_xy();                     // (a segment's chunks read its Ghat through one L2)
+  const int bh = gxy.y, hh = bh % a.H, n = a.n, nch = a.nch;
+  const int cb = gxy.x * C::CPB + cw;
   const T* omq_h = (const T*)a.omq + (size_t)hh * M * D;
   {
     StageRows<T, M, D, 64 * C::CPB * WPC> so;
@@ -1357,11 +1377,12 @@ __global__ __launch_bounds__(512) void k_bwd_keys(BwdArgs a, int nfb) {
   const T* ks = (const T*)a.k + seq * D;
   const T* vs = (const T*)a.v + seq * DV;
   const float* rx = a.rex + (size_t)bh * (nch + 1);
-  const float* G = a.gst + ((size_t)bh * nch + cbx) * S;    // Ghat_b [p][d], ghat [p]
-  const bool has_after = cbx < nch - 1;
+  const int sg = cbx / a.cpw;
+  const float* G = a.gst + ((size_t)bh * a.nseg + sg) * S;    // Ghat [p][d], ghat [p] of the chunk's segment
+  const bool has_after = sg < a.nseg - 1;
   const int j = s0 + col;
   const bool vt = active && j < n;
-  const float eps_j = (vt && has_after) ? fast_exp2(a.rj[seq + j] - rx[cbx + 1]) : 0.0f;
+  const float eps_j = (vt && has_after) ? fast_exp2(a.rj[seq + j] - rx[(sg + 1) * a.cpw]) : 0.0f;
 
   // ---- phase 1: per feature tile ----
   float sk = 0.0f;
@@ -1493,6 +1514,33 @@ static int launch_err(const char* what) {
   return 0;
 }
 
+// Workgroups of a kernel that run at once on the chip (256 CUs)
+template <typename K>
+static int64_t kernel_slots(K kernel, int threads) {
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kernel, threads, 0) != hipSuccess) per_cu = 0;
+  (void)hipGetLastError();
+  return 256 * (int64_t)(per_cu > 0 ? per_cu : 1);
+}
+
+// Chunks per workgroup of the state sweep (1, 2, 4 or 8).  A segment of several
+// chunks leaves one state gradient where each chunk left its own (written by
+// the sweep, read and written by the reverse scan, read twice by the key side:
+// about five passes over it at 4.9 TB/s), but takes the number of workgroups
+// down with it: rounds of `slots` workgroups, each about 0.8 us x D per chunk.
+// 2 x 16 heads x 16384 tokens, d = m = 128: reverse scan 0.49 -> 0.11 ms, key
+// side 0.74 -> 0.66 with four chunks, the sweep itself unchanged.
+static int state_segment(int nch, int64_t per_chunk, int64_t slots, int D, double state_bytes) {
+  int best = 1;
+  double best_t = 1e300;
+  for (int c = 1; c <= 8 && c <= nch; c *= 2) {
+    const int64_t nseg = (nch + c - 1) / c, wgs = nseg * per_chunk;
+    const double t = (double)((wgs + slots - 1) / slots) * c * 0.8e-6 * D + 5.0 * wgs * state_bytes / 4.9e12;
+    if (t < best_t) { best_t = t; best = c; }
+  }
+  return best;
+}
+
 template <typename T, int D, int DV, int M, int NA>
 static int run_bwd(const Shape& s, BwdArgs a, hipStream_t st) {
   using A = AsCfg<T, D, DV, M, NA>;
@@ -1501,6 +1549,10 @@ static int run_bwd(const Shape& s, BwdArgs a, hipStream_t st) {
   const int BH = (int)s.BH();
   const int nch = (int)s.nch();
   const size_t rows = (size_t)BH * s.n;
+  using St = StCfg<T, D, DV, M, NA>;
+  static const int64_t slots = kernel_slots(k_bwd_state<T, D, DV, M, NA>, 64 * St::NW);
+  a.cpw = state_segment(nch, (int64_t)BH * NFB, slots, D, St::FB * (DV + 1) * 4.0);
+  a.nseg = (nch + a.cpw - 1) / a.cpw;
   {
     ProfScope ps("bwd_prep", st);
     constexpr int RPB = 256 / (DV / (16 / (int)sizeof(T)));     // rows per block of k_bwd_rowprep
@@ -1516,7 +1568,7 @@ static int run_bwd(const Shape& s, BwdArgs a, hipStream_t st) {
   }
   if (int rc = launch_err("dqdr")) return rc;
   { ProfScope ps("bwd_state", st);
-  k_bwd_state<T, D, DV, M, NA><<<dim3(nch, BH, NFB), 64 * StCfg<T, D, DV, M, NA>::NW, 0, st>>>(a);
+  k_bwd_state<T, D, DV, M, NA><<<dim3(a.nseg, BH, NFB), 64 * St::NW, 0, st>>>(a);
   }
   if (int rc = launch_err("state")) return rc;
   constexpr int S = M * DV + M;

@@ -37,9 +37,9 @@ struct Workspace {
   float* rj;        // [BH][n]              running key frame R_j (log2)
   float* part;      // [m/128][BH][n][Dv+2] per-feature-block readout partials (m > 128)
   // backward-only regions (null in forward)
-  float* gstates;   // [BH][nch][m*Dv + m]  per-chunk state gradients, then reverse-scanned
-  float* dchi;      // [BH][n][m]           intra-chunk key-feature gradient (frame R_j)
-  float* dvin;      // [nfb][BH][n][Dv]     intra-chunk value gradient
+  float* gstates;   // [BH][<= nch][m*Dv + m] state gradient of each segment of chunks, then reverse-scanned
+  float* dchi;      // [BH][n][m]           intra-segment key-feature gradient (frame R_j)
+  float* dvin;      // [nfb][BH][n][Dv]     intra-segment value gradient
   float* du32;      // [nfb][BH][n][Dv]     du per feature block (m > 128 only)
   float* dr32;      // [nfb][BH][n][D]      dr per feature block (m > 128 only)
   float* dq32;      // [nfb][ns][BH][n][D]  dq partial of each anchor tile (slot = row chunk - anchor tile)

@@ -128,6 +128,13 @@ def test_backward_half_tile_rows(D, m, n, w, dt):
     _run(Workload("half_bwd", 1, 2, n, D, D, m, w, dt, "fwdbwd", seed=47))
 
 
+@pytest.mark.parametrize("B,H,n,D,m,dt", [(2, 16, 15987, 128, 128, "bf16"), (8, 16, 4040, 64, 64, "f32")])
+def test_backward_state_segments(B, H, n, D, m, dt):
+    """Enough workgroups for the state sweep to walk several chunks each, with a
+    short last segment and a ragged last chunk: one sampled (batch, head)."""
+    _run(Workload("segments_bwd", B, H, n, D, D, m, 64, dt, "fwdbwd", seed=48), pairs=[(B - 1, 3)])
+
+
 @pytest.mark.parametrize("D,m,n,w,dt", [(128, 128, 250, 64, "bf16"), (64, 64, 200, 40, "f32")])
 def test_backward_tile_grid_multiple_of_8(D, m, n, w, dt):
     """Tiles x heads a multiple of eight (here 8 x 4 and 7 x 8): the sweeps
