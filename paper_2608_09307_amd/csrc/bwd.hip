@@ -927,7 +927,17 @@ struct StCfg {
   static constexpr int PAD = MF<T>::PAD;
   static constexpr int FB = M < 128 ? M : 128;
   static constexpr int NFB = M / FB;
-  static constexpr int NW = FB / 32;
+  static constexpr int NP = FB / 32;                 // feature tiles
+  // Anchor groups: F is linear in the anchors, so below four feature tiles each
+  // anchor tile of a row gets a wave of its own per feature tile, with its part
+  // of F, and the parts of dchi, dv and GB are added through LDS.  One wave per
+  // feature tile left a workgroup of m <= 64 at one or two waves: a wide window
+  // (w = 100, d = 128, m = 64, 127 KB of LDS) ran half a wave per SIMD, 0.68 ms
+  // at 2 x 8 heads x 3001 tokens, now 0.52; float32 d = m = 64, w = 48, 8 heads
+  // x 1000 tokens 0.18 -> 0.11.
+  static constexpr int AH = NP < 4 ? NA : 1;
+  static constexpr int NAW = NA / AH;                // anchor tiles per wave
+  static constexpr int NW = NP * AH;
   static constexpr int AW = 32 * NA;                 // anchor offsets i - c per row
   static constexpr int WIN = 32 + AW - 1;            // anchor window rows of a chunk
   static constexpr int NT32 = (WIN + 31) / 32;
@@ -940,12 +950,11 @@ struct StCfg {
   // bytes after the u window (rows of pitch DV + tp)
   static constexpr int tail(int tp) {
     return a16(WIN * (DV + tp) * ES) + a16(32 * (FB + PAD) * ES) + a16(32 * AW * 4) + 2 * a16(32 * 4) +
-           a16(NW * D * ES) + a16(NW * RB * DV * 4);
+           a16(NW * D * ES) + a16(NW * RB * DV * 4) + (AH > 1 ? a16(NW * RB * 32 * 4) : 0);
   }
   // two workgroups per CU up to two anchor tiles per row (w <= 64); wider
   // windows stage up to 159 anchor rows and run one workgroup per CU
   static constexpr int LDS_CAP = NA <= 2 ? 80 * 1024 : 160 * 1024;
-  static constexpr int MINB = NA <= 2 ? 2 : 1;
   // full-rate transposing reads of u when the budget allows
   static constexpr int TP = (oU + tail(tr_pad<T, DV>()) <= LDS_CAP || sizeof(T) != 2) ? tr_pad<T, DV>() : 16;
   static constexpr int oChi = oU + a16(WIN * (DV + TP) * ES);
@@ -954,7 +963,13 @@ struct StCfg {
   static constexpr int oL = oRj + a16(32 * 4);
   static constexpr int oQ = oL + a16(32 * 4);
   static constexpr int oDv = oQ + a16(NW * D * ES);
-  static constexpr int BYTES = oDv + a16(NW * RB * DV * 4);
+  static constexpr int oDc = oDv + a16(NW * RB * DV * 4);
+  static constexpr int BYTES0 = oDc + (AH > 1 ? a16(NW * RB * 32 * 4) : 0);
+  static constexpr int RED = (AH - 1) * NP * 64 * (DV / 2 + 1) * 4;   // end-of-segment sum over the anchor groups
+  static constexpr int BYTES = BYTES0 > RED ? BYTES0 : RED;
+  // waves per SIMD (at most three, 168 registers) of the workgroups the LDS admits
+  static constexpr int PERCU = 160 * 1024 / BYTES;
+  static constexpr int WPE = PERCU * NW / 4 < 1 ? 1 : PERCU * NW / 4 < 3 ? PERCU * NW / 4 : 3;
 };
 
 template <typename T> LS_DEV void ld4f(const T* p, float (&x)[4]) {
@@ -985,10 +1000,11 @@ template <typename T> LS_DEV void sq_split(const typename MF<T>::frag& x, typena
 }
 
 template <typename T, int D, int DV, int M, int NA>
-__global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a) {
+__global__ __launch_bounds__((64 * StCfg<T, D, DV, M, NA>::NW), (StCfg<T, D, DV, M, NA>::WPE)) void k_bwd_state(BwdArgs a) {
   using F = MF<T>;
   using C = StCfg<T, D, DV, M, NA>;
   constexpr int PAD = C::PAD, FB = C::FB, WIN = C::WIN, NW = C::NW, AW = C::AW, RB = C::RB;
+  constexpr int NP = C::NP, AH = C::AH, NAW = C::NAW;
   constexpr int NT = 64 * NW;
   static_assert(C::BYTES <= C::LDS_CAP, "state LDS budget");
   __shared__ __align__(16) char smem[C::BYTES];
@@ -999,6 +1015,7 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
   float* sRj = (float*)(smem + C::oRj);
   float* sL = (float*)(smem + C::oL);
   float* sDv = (float*)(smem + C::oDv);        // [wave][row % RB][d] intra dv partials
+  float* sDc = (float*)(smem + C::oDc);        // [wave][row % RB][p] intra dchi partials (AH > 1)
 
   const int tid = threadIdx.x, l = tid & 63, col = l & 31, h = l >> 5, wv = uniform(tid >> 6);
   T* sQ = (T*)(smem + C::oQ) + wv * D;
@@ -1013,7 +1030,9 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
   const T* gs = (const T*)a.dout + seq * DV;
   const T* omq_h = (const T*)a.omq + (size_t)hh * M * D;
   const int w = a.w;
-  const int pw = fb * FB + wv * 32;            // first feature of this wave's tile
+  const int wp = wv % NP;                      // this wave's feature tile and anchor group
+  const int a0 = 32 * NAW * (wv / NP);         // first anchor offset of the group
+  const int pw = fb * FB + wp * 32;            // first feature of the tile
 
   f32x16 Fm[DV / 32];
 #pragma unroll
@@ -1027,7 +1046,8 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
   // formed in the chunk instead of being held in registers across chunks
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
-  tid &= NT - 1;                               // (its range, which the compiler no longer knows)
+  if constexpr ((NT & (NT - 1)) == 0) tid &= NT - 1;   // (its range, which the compiler no longer knows)
+  else __builtin_assume(tid >= 0 && tid < NT);
   const int l = tid & 63, col = l & 31, h = l >> 5;
   const int s0 = cb * 32;
   const int wb = s0 - (AW - 1);                // window row 0 = anchor s0 - (AW - 1)
@@ -1148,32 +1168,32 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
     if (t > 0) fetch(t - 1);
     const int i = s0 + t;
     wave_lds_sync();
-    // logits L[c, p] of the row's anchor tiles (regs <-> anchor c = i - 32an - crow)
-    f32x16 acc[NA];
+    // logits L[c, p] of the row's anchor tiles (regs <-> anchor c = i - a0 - 32an - crow)
+    f32x16 acc[NAW];
 #pragma unroll
-    for (int an = 0; an < NA; ++an) acc[an] = zero16();
+    for (int an = 0; an < NAW; ++an) acc[an] = zero16();
 #pragma unroll
     for (int s = 0; s < D / F::KS; ++s) {
       const int k0 = s * F::KS + h * F::KPL;
       if constexpr (sizeof(T) == 2) {
         const f16x8 bq = omf[s] * *(const f16x8*)((const f16*)sQ + k0);
 #pragma unroll
-        for (int an = 0; an < NA; ++an)
+        for (int an = 0; an < NAW; ++an)
           acc[an] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-              *(const f16x8*)((const f16*)sR + (t + AW - 1 - 32 * an - col) * (D + PAD) + k0), bq, acc[an], 0, 0, 0);
+              *(const f16x8*)((const f16*)sR + (t + AW - 1 - a0 - 32 * an - col) * (D + PAD) + k0), bq, acc[an], 0, 0, 0);
       } else {
         const float bq = omf[s] * F::ld(sQ, k0);
 #pragma unroll
-        for (int an = 0; an < NA; ++an)
-          acc[an] = F::mma(F::ld(sR + (t + AW - 1 - 32 * an - col) * (D + PAD), k0), bq, acc[an]);
+        for (int an = 0; an < NAW; ++an)
+          acc[an] = F::mma(F::ld(sR + (t + AW - 1 - a0 - 32 * an - col) * (D + PAD), k0), bq, acc[an]);
       }
     }
     // psi = 2^(L + bias); bias -inf outside the window
-    typename F::frag pf[NA][F::CSTEPS];
+    typename F::frag pf[NAW][F::CSTEPS];
     float ps = 0.0f;
 #pragma unroll
-    for (int an = 0; an < NA; ++an) {
-      const float* brow = sNz + t * AW + 32 * an + 4 * h;
+    for (int an = 0; an < NAW; ++an) {
+      const float* brow = sNz + t * AW + a0 + 32 * an + 4 * h;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const f32x4 b4 = *(const f32x4*)(brow + 8 * g);
@@ -1200,8 +1220,8 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
     for (int dt = 0; dt < DV / 32; ++dt) {
       f32x16 y = zero16();
 #pragma unroll
-      for (int an = 0; an < NA; ++an) {
-        auto rmap = [&](int ar) { return t + AW - 1 - 32 * an - ar; };
+      for (int an = 0; an < NAW; ++an) {
+        auto rmap = [&](int ar) { return t + AW - 1 - a0 - 32 * an - ar; };
 #pragma unroll
         for (int sp = 0; sp < F::CSTEPS; ++sp)
           y = F::mma(pf[an][sp], F::tld_crow_map(sU, DV + C::TP, sp, dt * 32, rmap), y);
@@ -1221,13 +1241,16 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
     const float xs = half_reduce16(X);
     const int pl = crow(col >> 1, h);
     const float ft = __shfl(half_swap_add(fpart), pl);
-    if ((col & 1) == 0) a.dchi[(seq + i) * M + pw + pl] = xs + ft;
+    if ((col & 1) == 0) {
+      if constexpr (AH == 1) a.dchi[(seq + i) * M + pw + pl] = xs + ft;
+      else sDc[(wv * RB + t % RB) * 32 + pl] = xs + ft;      // this anchor group's part
+    }
     // intra dv_t[d] = sum_p chi_t[p] F_t[p, d]  (this wave's p tile; summed over waves below)
     float chv[16];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       float c4[4];
-      ld4f<T>(sChi + t * (FB + PAD) + F::sigma(wv * 32 + 8 * g + 4 * h), c4);
+      ld4f<T>(sChi + t * (FB + PAD) + F::sigma(wp * 32 + 8 * g + 4 * h), c4);
 #pragma unroll
       for (int e = 0; e < 4; ++e) chv[4 * g + e] = c4[e];
     }
@@ -1251,6 +1274,17 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
           dvin[(size_t)(s0 + t + rr) * DV + d] = x;
         }
       }
+      if constexpr (AH > 1) {
+        for (int idx = tid; idx < RB * FB; idx += NT) {
+          const int rr = idx / FB, p = idx % FB;
+          if (t + rr <= tlast) {
+            float x = 0.0f;
+#pragma unroll
+            for (int ah = 0; ah < AH; ++ah) x += sDc[((ah * NP + p / 32) * RB + rr) * 32 + p % 32];
+            a.dchi[(seq + s0 + t + rr) * M + fb * FB + p] = x;
+          }
+        }
+      }
       __syncthreads();
     }
   }
@@ -1262,11 +1296,35 @@ __global__ __launch_bounds__(256, (NA <= 2 ? 2 : 1)) void k_bwd_state(BwdArgs a)
   float* g = a.gst + ((size_t)bh * a.nseg + sg) * S;
   const float Rexb = a.rex[(size_t)bh * (nch + 1) + cbf];
   const float fac = fast_exp2(Rexb - Rnext);   // 0 for the first chunk (Rex_0 = -inf)
+  float ft = half_swap_add(fpart);
+  if constexpr (AH > 1) {
+    // the anchor groups' parts, added in order
+    float* red = (float*)smem;
+    constexpr int PL = 64 * (DV / 2 + 1);
+    if (wv >= NP) {
+      float* dst = red + (wv - NP) * PL + l;
+#pragma unroll
+      for (int dt = 0; dt < DV / 32; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) dst[64 * (16 * dt + v)] = Fm[dt][v];
+      dst[64 * (DV / 2)] = ft;
+    }
+    __syncthreads();
+    if (wv >= NP) return;
+#pragma unroll
+    for (int ah = 1; ah < AH; ++ah) {
+      const float* src = red + ((ah - 1) * NP + wv) * PL + l;
+#pragma unroll
+      for (int dt = 0; dt < DV / 32; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) Fm[dt][v] += src[64 * (16 * dt + v)];
+      ft += src[64 * (DV / 2)];
+    }
+  }
 #pragma unroll
   for (int dt = 0; dt < DV / 32; ++dt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) g[(size_t)(pw + crow(v, h)) * DV + dt * 32 + col] = Fm[dt][v] * fac;
-  const float ft = half_swap_add(fpart);
   if (h == 0) g[(size_t)M * DV + pw + col] = ft * fac;
 }
 
@@ -1527,7 +1585,8 @@ static int64_t kernel_slots(K kernel, int threads) {
 // chunks leaves one state gradient where each chunk left its own (written by
 // the sweep, read and written by the reverse scan, read twice by the key side:
 // about five passes over it at 4.9 TB/s), but takes the number of workgroups
-// down with it: rounds of `slots` workgroups, each about 0.8 us x D per chunk.
+// down with it: rounds of `slots` workgroups, each about 0.8 us x D per chunk,
+// and an uneven end of about 0.3 of a workgroup.
 // 2 x 16 heads x 16384 tokens, d = m = 128: reverse scan 0.49 -> 0.11 ms, key
 // side 0.74 -> 0.66 with four chunks, the sweep itself unchanged.
 static int state_segment(int nch, int64_t per_chunk, int64_t slots, int D, double state_bytes) {
@@ -1535,7 +1594,7 @@ static int state_segment(int nch, int64_t per_chunk, int64_t slots, int D, doubl
   double best_t = 1e300;
   for (int c = 1; c <= 8 && c <= nch; c *= 2) {
     const int64_t nseg = (nch + c - 1) / c, wgs = nseg * per_chunk;
-    const double t = (double)((wgs + slots - 1) / slots) * c * 0.8e-6 * D + 5.0 * wgs * state_bytes / 4.9e12;
+    const double t = ((double)((wgs + slots - 1) / slots) + 0.3) * c * 0.8e-6 * D + 5.0 * wgs * state_bytes / 4.9e12;
     if (t < best_t) { best_t = t; best = c; }
   }
   return best;
