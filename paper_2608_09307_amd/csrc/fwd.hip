@@ -35,6 +35,10 @@ struct FwdArgs {
   void* chi;          // [BH][n][m] key features 2^(lambda_j - R_j)/sqrt(m), p permuted in 16-blocks
   float* rj;          // [BH][n]    running key frame R_j (log2)
   int H; int n; int w; int nch; int BH; float eps;
+  // bf16 scan in segments (G > 1): chunks per segment; [BH][G-1][m*Dv] states of
+  // the segments before the last (matrix-core tiles), [BH][G-1][m], [BH][G-1]
+  int G; int cps;
+  float* seg_M; float* seg_a; float* seg_R;
 };
 
 // ---------------------------------------------------------------------------
@@ -317,34 +321,36 @@ __global__ __launch_bounds__(256) void k_keyfeat(FwdArgs a) {
 // first 32 columns also scans a in place.  Workgroups are dealt to the eight
 // XCDs in turn; the waves of one sequence-head are numbered to land on one XCD,
 // so the fragments they share come through one L2.
+// A wave's chain is one chunk after the other (0.55-0.7 us each), so a short
+// batch is cut into G segments: k_scan_totals forms each segment's state, and
+// every segment's scan starts from the sum of those before it.
 // [App. C "Host preparation": exclusive cumulative sum -> boundary states]
 // ---------------------------------------------------------------------------
+// A wave's place: sequence-head, state tile (features p0.., columns d0..) and segment
 template <int M, int DV>
-__global__ __launch_bounds__(64) void k_state_scan_mma(FwdArgs a) {
-  constexpr int S = M * DV + M;
-  constexpr int NDT = DV / 32, NPD = (M / 32) * NDT;
-  constexpr int PF = 6;
-  // the state tile passes through LDS so that each lane stores 32 contiguous
-  // bytes (16 two-byte stores per lane would take most of the memory counter
-  // that the loads in flight need)
-  __shared__ __align__(16) bf16 sT[32][40];
-  const int l = threadIdx.x, col = l & 31, h = l >> 5;
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int bh = xcd + 8 * (slot / NPD), tt = slot % NPD;
-  if (bh >= a.BH) return;                              // wave-uniform
-  const int p0 = (tt / NDT) * 32, d0 = (tt % NDT) * 32;
-  const int nch = a.nch;
-  float* stb = a.states + (size_t)bh * nch * S;
-  bf16* s16 = (bf16*)a.states16 + (size_t)bh * nch * M * DV;
-  const float* rh = a.rho + (size_t)bh * nch;
-  float* rx = a.rex + (size_t)bh * (nch + 1);
-  const bool aw = d0 == 0;                              // also scans a (lanes of half 0)
-  const bool writer = p0 == 0 && d0 == 0 && l == 0;
+struct ScanPlace {
+  static constexpr int NDT = DV / 32, NPD = (M / 32) * NDT;
+  int bh, tt, g, p0, d0;
+  LS_DEV explicit ScanPlace(int nseg) {
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    g = slot % nseg;
+    tt = (slot / nseg) % NPD;
+    bh = xcd + 8 * (slot / (nseg * NPD));
+    p0 = (tt / NDT) * 32;
+    d0 = (tt % NDT) * 32;
+  }
+};
+
+// The operands of chunk b's contribution to a wave's tile, PF chunks in flight:
+// every load unconditional (clamped chunk index), so that the compiler's
+// memory-counter waits see them all
+template <int M, int DV, int PF>
+struct ScanRing {
   bf16x8 xq[PF][4];
   float aq[PF], rq[PF];
-  // every load unconditional (clamped chunk index), so that the compiler's
-  // memory-counter waits see PF chunks in flight
-  auto fetch = [&](int b, int e) {
+  LS_DEV void fetch(const float* stb, const float* rh, int p0, int d0, int b, int e) {
+    constexpr int S = M * DV + M;
+    const int l = threadIdx.x, col = l & 31, h = l >> 5;
     const bf16* cx = (const bf16*)(stb + (size_t)b * S);
     const bf16* vx = cx + M * 32;
     xq[e][0] = *(const bf16x8*)(cx + (p0 + col) * 32 + 8 * h);
@@ -353,11 +359,97 @@ __global__ __launch_bounds__(64) void k_state_scan_mma(FwdArgs a) {
     xq[e][3] = *(const bf16x8*)(vx + (d0 + col) * 32 + 16 + 8 * h);
     aq[e] = stb[(size_t)b * S + M * DV + p0 + col];
     rq[e] = rh[b];
-  };
+  }
+  // run, runa, R <- the state with chunk b's contribution (ring slot e)
+  LS_DEV void add(int e, f32x16& run, float& runa, float& R) const {
+    f32x16 c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xq[e][0], xq[e][2], zero16(), 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xq[e][1], xq[e][3], c, 0, 0, 0);
+    const float rb = uniform(rq[e]);
+    const float Rn = fmaxf(R, rb);
+    const float sa = fast_exp2(R - Rn);                // 0 when R = -inf
+    const float sb = fast_exp2(rb - Rn);
 #pragma unroll
-  for (int e = 0; e < PF; ++e) fetch(min(e, nch - 1), e);
+    for (int v = 0; v < 16; ++v) run[v] = run[v] * sa + c[v] * sb;
+    runa = runa * sa + aq[e] * sb;
+    R = Rn;
+  }
+};
+
+// The state of every segment but the last, one wave per (sequence-head, tile,
+// segment), tiles as the accumulator holds them
+template <int M, int DV>
+__global__ __launch_bounds__(64) void k_scan_totals(FwdArgs a) {
+  constexpr int S = M * DV + M, PF = 6;
+  using P = ScanPlace<M, DV>;
+  const P w(a.G - 1);
+  if (w.bh >= a.BH) return;                            // wave-uniform
+  const int l = threadIdx.x, col = l & 31, h = l >> 5;
+  const int b0 = w.g * a.cps, b1 = b0 + a.cps;         // (whole segments: only the last may be short)
+  const float* stb = a.states + (size_t)w.bh * a.nch * S;
+  const float* rh = a.rho + (size_t)w.bh * a.nch;
+  ScanRing<M, DV, PF> ring;
+#pragma unroll
+  for (int e = 0; e < PF; ++e) ring.fetch(stb, rh, w.p0, w.d0, min(b0 + e, b1 - 1), e);
   f32x16 run = zero16();
   float runa = 0.0f, R = kNegInf;
+  int b = b0;
+  for (; b + PF <= b1; b += PF) {
+#pragma unroll
+    for (int e = 0; e < PF; ++e) {
+      ring.add(e, run, runa, R);
+      ring.fetch(stb, rh, w.p0, w.d0, min(b + e + PF, b1 - 1), e);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < PF; ++e)
+    if (b + e < b1) ring.add(e, run, runa, R);
+  const size_t sg = (size_t)w.bh * (a.G - 1) + w.g;
+  float* o = a.seg_M + (sg * P::NPD + w.tt) * 1024 + l * 4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) *(f32x4*)(o + 256 * q) = f32x4{run[4 * q], run[4 * q + 1], run[4 * q + 2], run[4 * q + 3]};
+  if (w.d0 == 0 && h == 0) a.seg_a[sg * M + w.p0 + col] = runa;
+  if (w.tt == 0 && l == 0) a.seg_R[sg] = R;
+}
+
+template <int M, int DV>
+__global__ __launch_bounds__(64) void k_state_scan_mma(FwdArgs a) {
+  constexpr int S = M * DV + M, PF = 6;
+  using P = ScanPlace<M, DV>;
+  // the state tile passes through LDS so that each lane stores 32 contiguous
+  // bytes (16 two-byte stores per lane would take most of the memory counter
+  // that the loads in flight need)
+  __shared__ __align__(16) bf16 sT[32][40];
+  const P w(a.G);
+  if (w.bh >= a.BH) return;                            // wave-uniform
+  const int l = threadIdx.x, col = l & 31, h = l >> 5;
+  const int bh = w.bh, p0 = w.p0, d0 = w.d0, nch = a.nch;
+  const int bs = w.g * a.cps, be = min(bs + a.cps, nch);
+  float* stb = a.states + (size_t)bh * nch * S;
+  bf16* s16 = (bf16*)a.states16 + (size_t)bh * nch * M * DV;
+  const float* rh = a.rho + (size_t)bh * nch;
+  float* rx = a.rex + (size_t)bh * (nch + 1);
+  const bool aw = d0 == 0;                              // also scans a (lanes of half 0)
+  const bool writer = w.tt == 0 && l == 0;
+  ScanRing<M, DV, PF> ring;
+#pragma unroll
+  for (int e = 0; e < PF; ++e) ring.fetch(stb, rh, p0, d0, min(bs + e, be - 1), e);
+  f32x16 run = zero16();
+  float runa = 0.0f, R = kNegInf;
+  // the segments before this one
+#pragma unroll 2
+  for (int g = 0; g < w.g; ++g) {
+    const size_t sg = (size_t)bh * (a.G - 1) + g;
+    const float* x = a.seg_M + (sg * P::NPD + w.tt) * 1024 + l * 4;
+    f32x4 t[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) t[q] = *(const f32x4*)(x + 256 * q);
+    const float ta = a.seg_a[sg * M + p0 + col], rb = a.seg_R[sg];
+    const float Rn = fmaxf(R, rb), sa = fast_exp2(R - Rn), sb = fast_exp2(rb - Rn);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) run[v] = run[v] * sa + t[v >> 2][v & 3] * sb;
+    runa = runa * sa + ta * sb;
+    R = Rn;
+  }
   // chunk b from ring slot e, then slot e takes chunk b + PF
   auto step = [&](int b, int e) {
     // the state of every token before chunk b (frame R)
@@ -373,27 +465,18 @@ __global__ __launch_bounds__(64) void k_state_scan_mma(FwdArgs a) {
     }
     if (aw) stb[(size_t)b * S + M * DV + p0 + col] = runa;   // both halves: the same value
     if (writer) rx[b] = R;
-    f32x16 c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xq[e][0], xq[e][2], zero16(), 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xq[e][1], xq[e][3], c, 0, 0, 0);
-    const float rb = uniform(rq[e]);
-    const float Rn = fmaxf(R, rb);
-    const float sa = fast_exp2(R - Rn);                // 0 when R = -inf
-    const float sb = fast_exp2(rb - Rn);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) run[v] = run[v] * sa + c[v] * sb;
-    runa = runa * sa + aq[e] * sb;
-    R = Rn;
-    fetch(min(b + PF, nch - 1), e);
+    ring.add(e, run, runa, R);
+    ring.fetch(stb, rh, p0, d0, min(b + PF, be - 1), e);
   };
-  int b0 = 0;
-  for (; b0 + PF <= nch; b0 += PF) {
+  int b0 = bs;
+  for (; b0 + PF <= be; b0 += PF) {
 #pragma unroll
     for (int e = 0; e < PF; ++e) step(b0 + e, e);
   }
 #pragma unroll
   for (int e = 0; e < PF; ++e)
-    if (b0 + e < nch) step(b0 + e, e);
-  if (writer) rx[nch] = R;
+    if (b0 + e < be) step(b0 + e, e);
+  if (writer && be == nch) rx[nch] = R;
 }
 
 // ---------------------------------------------------------------------------
@@ -781,6 +864,30 @@ __global__ __launch_bounds__(256) void k_merge_blocks(FwdArgs a) {
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
+// Segments of the bf16 scan: the count that minimises the estimated time of the
+// scan (a chunk's step 0.6 us in each wave's chain, or its bytes at 4.5 TB/s)
+// and, for more than one segment, of the totals before it (0.35 us a chunk, or
+// the operands' bytes, the launch, the earlier segments' states), at most
+// room + 1 of them.  4 x 8 heads x 2048 tokens, d = m = 64: 33 -> 20 us with
+// both kernels; 2 x 8 x 3001, d = 128, m = 64: 48 -> 25.  Above 64 MB of
+// operands and states, which the caches no longer hold, the chains of many
+// segments only share the memory: 2 x 16 x 16384, d = m = 128, 0.36 ms whole
+// and 0.47 in two; 8 x 6 x 2048, d = 64, m = 128 (88 MB), 35 us and 39.
+static int scan_segments(int nch, int64_t room, int BH, int M, int DV) {
+  const double frag = 64.0 * BH * nch * (M + DV), out = 2.0 * BH * nch * M * DV;
+  if (frag + out > 64e6) return 1;
+  int best = 1;
+  double best_t = 1e300;
+  for (int G = 1; G <= 32 && G <= room + 1 && G <= nch; ++G) {
+    const int cps = (nch + G - 1) / G;
+    if ((nch + cps - 1) / cps != G) continue;              // the last segment would be empty
+    double t = fmax(cps * 0.6, (frag + out) / 4.5e6);
+    if (G > 1) t += fmax(cps * 0.35, frag / 4.5e6) + 5.0 + 0.3 * G;
+    if (t < best_t) { best_t = t; best = G; }
+  }
+  return best;
+}
+
 template <typename T, int D, int DV, int M, int NA>
 static int run_fwd(const Shape& s, FwdArgs a, hipStream_t st) {
   // readout waves per workgroup: the workgroup's LDS fills a CU, so its wave
@@ -799,8 +906,20 @@ static int run_fwd(const Shape& s, FwdArgs a, hipStream_t st) {
   k_chunk_state<T, D, DV, M><<<dim3((nch + 3) / 4, BH), 256, 0, st>>>(a); }
   if constexpr (sizeof(T) == 2) {
     constexpr int NPD = (M / 32) * (DV / 32);
+    const unsigned waves = (unsigned)((BH + 7) / 8 * 8 * NPD);
+    // the segments' states use the space of chi, which k_keyfeat fills after the scan
+    const int64_t room = (int64_t)s.n * M * (int)sizeof(T) / (4 * (M * DV + M + 1));
+    a.G = scan_segments(nch, room, BH, M, DV);
+    a.cps = (nch + a.G - 1) / a.G;
+    a.seg_M = (float*)a.chi;
+    a.seg_a = a.seg_M + (size_t)BH * (a.G - 1) * M * DV;
+    a.seg_R = a.seg_a + (size_t)BH * (a.G - 1) * M;
+    if (a.G > 1) {
+      ProfScope ps("scan_totals", st);
+      k_scan_totals<M, DV><<<waves * (a.G - 1), 64, 0, st>>>(a);
+    }
     ProfScope ps("state_scan", st);
-    k_state_scan_mma<M, DV><<<(unsigned)((BH + 7) / 8 * 8 * NPD), 64, 0, st>>>(a);
+    k_state_scan_mma<M, DV><<<waves * a.G, 64, 0, st>>>(a);
   } else {
     constexpr int S = M * DV + M;
     ProfScope ps("state_scan", st);

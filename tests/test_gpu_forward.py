@@ -137,3 +137,15 @@ def test_forward_two_feature_blocks_short_windows(w, n):
     """m = 256 (feature-block partials merged by the online maximum) with one
     anchor tile per row, w = 1 included."""
     _run_and_compare(Workload("m256_short_w_fwd", 1, 2, n, 128, 128, 256, w, "bf16", "fwd", seed=37))
+
+
+@pytest.mark.parametrize("D,m,B,H,n", [
+    (64, 64, 1, 1, 1601),     # 51 chunks in segments, the last one short, one token in the last chunk
+    (128, 256, 1, 2, 1300),   # no room for more than a few segments' states beside the key features
+    (32, 32, 3, 3, 900),      # heads that leave slots of the last XCD round empty
+    (128, 128, 1, 1, 2048),
+])
+def test_scan_segments(D, m, B, H, n):
+    """Few heads and many chunks: the state scan runs in segments whose totals a
+    kernel before it forms (keys boosted so that frames differ between segments)."""
+    _run_and_compare(Workload("scan_fwd", B, H, n, D, D, m, 64, "bf16", "fwd", seed=49, boost_frac=0.4, boost=2.0))
