@@ -1,5 +1,5 @@
-// LinSimp autoregressive decode step on gfx950 (Theorem 1: the persistent
-// state of a head is M, a and the last w anchor rows (r_c, u_c)).
+// LinSimp autoregressive decode on gfx950 (Theorem 1: the persistent state of a
+// head is M, a and the last w anchor rows (r_c, u_c)).
 //
 // Per (sequence s, head h), token t = pos[s]:
 //   lambda = log2-features of k_t;  R' = max(R, max_p lambda_p)
@@ -26,700 +26,382 @@ struct DecArgs {
   int H; int w; float eps;
 };
 
-template <typename T, int D, int DV, int M, int NA, bool OM_LDS = true>
+// ---------------------------------------------------------------------------
+// Decode: ntok tokens per sequence in one launch (token j of sequence s is
+// position pos[s] + j), in blocks of TB: TB = 1 for the single step, whose
+// token loop unrolls away, 8 otherwise; a token's arithmetic is the same in
+// both, so T tokens in one call give the bits of T single steps.  One workgroup
+// per (sequence, head), one wave per 32 features; each wave keeps its rows of M
+// and of the bank (float32) in registers, its entries of a, and a row shift L_w
+// of its own (over its features only), so the waves walk the tokens of a block
+// without meeting; the parts of N and Z are brought together, in order, once
+// per block.
+//
+// The anchors r, u of the last 32 NA - 1 tokens and of the block's tokens sit in
+// LDS, one row per token in a ring of E = 32 NA + TB rows: token i of the call
+// (i < 0: before it) has row (i + 32 NA) mod E, and its anchor at offset dl the
+// row of token i - dl.  Per block: lambda by float32 dot products (their maxima
+// give every token's frame R) and the table of |z|^2.  Per token and wave: the
+// state update, the logits L[c, p] = sum_d r_c[d] (q[d] Omega[p, d]) with
+// q (*) Omega rounded once, psi = 2^(L - |z|^2 log2(e)/2 - L_w), W = Psi^T U on
+// the matrix cores, N += M (*) W.
+//
+// Several tokens: bound by the per-token work of two waves per SIMD (about 620
+// VALU instructions and 32 matrix products each).  A form that met at five
+// barriers per token (key frame, row shift, sums), formed z = q (*) r in every
+// wave and read the bank from L2 for each token took 161 us for 16 tokens of
+// 32 sequences x 16 heads (d = m = 128, w = 64), this one 89.  A single step
+// moves each state element once: 256 x 16 at d = m = 128 0.145 ms, 4.8 TB/s,
+// the rate of a copy.
+// ---------------------------------------------------------------------------
+template <typename T, int D, int DV, int M, int NA, int TB>
 struct DCfg {
-  static constexpr int PAD = MF<T>::PAD;
-  static constexpr int W = 32 * NA;
+  static constexpr int NW = M / 32, NT = 64 * NW;
+  static constexpr int AW = 32 * NA, E = AW + TB;
+  static constexpr int RST = D + MF<T>::PAD, UST = DV + tr_pad<T, DV>();
   static constexpr int ES = sizeof(T);
   static constexpr int a16(int x) { return (x + 15) & ~15; }
-  static constexpr int oOm = 0;                         // Omega * log2 e (when staged in LDS)
-  static constexpr int oRr = oOm + (OM_LDS ? a16(M * (D + PAD) * ES) : 0);
-  static constexpr int oUt = oRr + a16(W * (D + PAD) * ES);
-  static constexpr int oQ = oUt + a16(DV * (W + PAD) * ES);
-  static constexpr int oK = oQ + a16(D * 4);
-  static constexpr int oV = oK + a16(D * 4);
-  static constexpr int oChi = oV + a16(DV * 4);
-  static constexpr int oAn = oChi + a16(M * 4);
-  static constexpr int oNz = oAn + a16(M * 4);
-  static constexpr int oRed = oNz + a16(W * 4);
-  static constexpr int oN = oRed + a16(64 * 4);
-  static constexpr int BYTES = oN + a16(4 * DV * 4);
+  static constexpr int oR = 0;                                   // r rows of the ring
+  static constexpr int oU = oR + a16(E * RST * ES);              // u rows (read transposed)
+  static constexpr int oQ = oU + a16(E * UST * ES);              // float32 q, k, v of the block
+  static constexpr int oK = oQ + a16(TB * D * 4);
+  static constexpr int oV = oK + a16(TB * D * 4);
+  static constexpr int oNz = oV + a16(TB * DV * 4);              // [j][dl]: -|z|^2 log2(e)/2, -inf if not a pair
+  static constexpr int oLam = oNz + a16(TB * AW * 4);            // [wave][j][32]: key log2-features
+  static constexpr int oChi = oLam + a16(NW * TB * 32 * 4);      // per wave: chi of its features
+  static constexpr int oN = oChi + a16(NW * 32 * 4);             // [wave][j][d]: N in the wave's row shift
+  static constexpr int oZ = oN + a16(NW * TB * DV * 4);          // [wave][j]: Z, L_w, largest lambda
+  static constexpr int BYTES = oZ + a16(3 * NW * TB * 4);
 };
 
-// LDS staging of a ring in two phases, so that a caller issues every global
-// load of its staging before the first LDS store (one memory round trip per
-// call, not one per staged array).  Ring rows c < nv come from `ring`
-// ([w][COLS]), row `slot` from `fresh` when it is given; rows nv .. ROWS-1
-// (nv <= w: past the window, or slots that hold no token yet) are zero, so
-// that a product with them needs no mask.  TRANS stores column-major with
-// the row index permuted by MF<T>::sigma (the readout's anchor operand layout).
-template <typename T, int ROWS, int COLS, bool TRANS>
-struct RingStage {
-  static constexpr int VE = 16 / sizeof(T);
-  static constexpr int CPR = COLS / VE;
-  static constexpr int N = ROWS * CPR;
-  static constexpr int IT = (N + 255) / 256;
-  typedef T V __attribute__((ext_vector_type(VE)));
-  V x[IT];
-  // unconditional loads (row clamped into the ring)
-  LS_DEV void load(const T* ring, const T* fresh, int slot, int w, int tid) {
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int idx = min(tid + 256 * it, N - 1), c = idx / CPR, e = (idx % CPR) * VE;
-      const int cr = c < w ? c : w - 1;
-      x[it] = *(const V*)((fresh != nullptr && cr == slot) ? fresh + e : ring + (size_t)cr * COLS + e);
-    }
-  }
-  LS_DEV void store(T* dst, int ldst, int nv, int tid) {
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int idx = tid + 256 * it, c = idx / CPR, e = (idx % CPR) * VE;
-      if (N % 256 != 0 && idx >= N) continue;
-      if (c >= nv) {
-#pragma unroll
-        for (int k = 0; k < VE; ++k) x[it][k] = (T)0.0f;
-      }
-      if constexpr (TRANS) {
-#pragma unroll
-        for (int k = 0; k < VE; ++k) dst[(e + k) * ldst + MF<T>::sigma(c)] = x[it][k];
-      } else {
-#pragma unroll
-        for (int k = 0; k < VE; ++k) dst[c * ldst + e + k] = x[it][k];
-      }
-    }
-  }
-};
-
-// Omega * log2(e) of one head into LDS rows of pitch D + PAD, operand type
-template <typename T, int D, int M>
-LS_DEV void stage_omega(T* dst, const float* om, int tid) {
-  constexpr int N = M * D / 4;
-  constexpr int IT = N / 256;
-  static_assert(N % 256 == 0, "Omega staging");
-#pragma unroll 8
-  for (int it = 0; it < IT; ++it) {
-    const int idx = tid + 256 * it, p = idx / (D / 4), e = (idx % (D / 4)) * 4;
-    const f32x4 x = *(const f32x4*)(om + (size_t)p * D + e);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) dst[p * (D + MF<T>::PAD) + e + k] = (T)(x[k] * kLog2e);
-  }
-}
-
-// Omega rows of one token's key GEMV held by this thread (M <= 128): feature
-// p = 32 wv + col, the KPL-wide pieces at k0 = ks KS + h KPL.  Loaded apart
-// from the GEMV so that a caller can issue the loads early.
-template <typename T, int D>
-struct KeyBankRows {
-  float o[D / MF<T>::KS][MF<T>::KPL];
-  LS_DEV void load(const float* om, int M, int tid) {
-    using F = MF<T>;
-    const int l = tid & 63, col = l & 31, h = l >> 5, wv = tid >> 6;
-    const int p = wv * 32 + col;
-    const float* orow = om + (size_t)(p < M ? p : 0) * D;
-#pragma unroll
-    for (int ks = 0; ks < D / F::KS; ++ks) {
-      const int k0 = ks * F::KS + h * F::KPL;
-      if constexpr (F::KPL % 4 == 0) {
-#pragma unroll
-        for (int e4 = 0; e4 < F::KPL; e4 += 4) {
-          const f32x4 x = *(const f32x4*)(orow + k0 + e4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) o[ks][e4 + e] = x[e];
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < F::KPL; ++e) o[ks][e] = orow[k0 + e];
-      }
-    }
-  }
-};
-
-// Log2 key features of one token, lambda_p = (omega_p . k - |k|^2 / 2) log2(e),
-// in float32 into lam[p] (LDS, p < M), from Omega rows already loaded
-// (M <= 128).  Feature p's dot product is split over lanes l and l ^ 32, which
-// take the alternate KPL-wide pieces of D that make up an MFMA operand
-// fragment of row p; with FRAGS the fragments of Omega * log2(e) in the
-// operand type are kept in omf[D / KS] for the query logits, so the bank is
-// read once.  Returns max_p lambda_p; every thread calls it (it ends with a
-// barrier).
-template <typename T, int D, int M, bool FRAGS>
-LS_DEV float key_log2_features_rows(const KeyBankRows<T, D>& kb, const float* sk, float* lam, float* sred,
-                                    typename MF<T>::frag* omf) {
+template <typename T, int D, int DV, int M, int NA, int TB>
+__global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int ntok) {
   using F = MF<T>;
-  static_assert(M <= 128, "one feature row per thread");
-  const int tid = threadIdx.x, l = tid & 63, col = l & 31, h = l >> 5, wv = tid >> 6;
-  float nk = 0.0f;
-#pragma unroll
-  for (int e = l; e < D; e += 64) nk += sk[e] * sk[e];
-  nk = wave_sum(nk);
-  float mx = kNegInf;
-  const int p = wv * 32 + col;
-  float acc = 0.0f;
-#pragma unroll
-  for (int ks = 0; ks < D / F::KS; ++ks) {
-    const int k0 = ks * F::KS + h * F::KPL;
-#pragma unroll
-    for (int e = 0; e < F::KPL; ++e) acc += kb.o[ks][e] * sk[k0 + e];
-    if constexpr (FRAGS) {
-      if constexpr (sizeof(T) == 2) {
-#pragma unroll
-        for (int e = 0; e < F::KPL; ++e) omf[ks][e] = (T)(kb.o[ks][e] * kLog2e);
-      } else {
-        omf[ks] = kb.o[ks][0] * kLog2e;
-      }
-    }
-  }
-  acc = half_swap_add(acc);
-  const float x = (acc - 0.5f * nk) * kLog2e;
-  if (p < M) {
-    mx = x;
-    if (h == 0) lam[p] = x;
-  }
-  mx = wave_max(mx);
-  if (l == 0) sred[wv] = mx;
-  __syncthreads();
-  return fmaxf(fmaxf(sred[0], sred[1]), fmaxf(sred[2], sred[3]));
-}
-
-// The same, loading the bank itself; any M (feature blocks of 128)
-template <typename T, int D, int M, bool FRAGS>
-LS_DEV float key_log2_features(const float* sk, const float* om, float* lam, float* sred,
-                               typename MF<T>::frag* omf) {
-  using F = MF<T>;
-  static_assert(!FRAGS || M <= 128, "fragments for one feature tile per wave");
-  if constexpr (M <= 128) {
-    KeyBankRows<T, D> kb;
-    kb.load(om, M, threadIdx.x);
-    return key_log2_features_rows<T, D, M, FRAGS>(kb, sk, lam, sred, omf);
-  } else {
-    static_assert(M % 128 == 0, "whole feature blocks");
-    const int tid = threadIdx.x, l = tid & 63, col = l & 31, h = l >> 5, wv = tid >> 6;
-    float nk = 0.0f;
-#pragma unroll
-    for (int e = l; e < D; e += 64) nk += sk[e] * sk[e];
-    nk = wave_sum(nk);
-    float mx = kNegInf;
-#pragma unroll
-    for (int p0 = 0; p0 < M; p0 += 128) {
-      const int p = p0 + wv * 32 + col;
-      const float* orow = om + (size_t)p * D;
-      float acc = 0.0f;
-#pragma unroll
-      for (int ks = 0; ks < D / F::KS; ++ks) {
-        const int k0 = ks * F::KS + h * F::KPL;
-        float o[F::KPL];
-        if constexpr (F::KPL % 4 == 0) {
-#pragma unroll
-          for (int e4 = 0; e4 < F::KPL; e4 += 4) {
-            const f32x4 x = *(const f32x4*)(orow + k0 + e4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e4 + e] = x[e];
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < F::KPL; ++e) o[e] = orow[k0 + e];
-        }
-#pragma unroll
-        for (int e = 0; e < F::KPL; ++e) acc += o[e] * sk[k0 + e];
-      }
-      acc = half_swap_add(acc);
-      const float x = (acc - 0.5f * nk) * kLog2e;
-      mx = fmaxf(mx, x);
-      if (h == 0) lam[p] = x;
-    }
-    mx = wave_max(mx);
-    if (l == 0) sred[wv] = mx;
-    __syncthreads();
-    return fmaxf(fmaxf(sred[0], sred[1]), fmaxf(sred[2], sred[3]));
-  }
-}
-
-// z = q (*) r of one anchor at one k-step as an operand fragment (q float32
-// in LDS, read in full for every lane), its |z|^2 summed into nz
-template <typename T>
-LS_DEV void composite_query(const float* q, const typename MF<T>::frag& rf, float& nz, typename MF<T>::frag& zf) {
-  if constexpr (sizeof(T) == 2) {
-    const f32x4 q0 = *(const f32x4*)q, q1 = *(const f32x4*)(q + 4);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float p = (e < 4 ? q0[e] : q1[e - 4]) * fel(rf, e);
-      nz += p * p;
-      zf[e] = (bf16)p;
-    }
-  } else {
-    const float p = q[0] * rf;
-    nz += p * p;
-    zf = p;
-  }
-}
-
-template <typename T, int D, int DV, int M, int NA>
-// two waves per SIMD where the LDS allows two workgroups per CU (m <= 128)
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(M > 128 ? 1 : 2))) void k_decode(DecArgs A) {
-  using F = MF<T>;
-  constexpr int PT = M / 32;                  // feature tiles
-  constexpr int PTW = (PT + 3) / 4;           // feature tiles per wave
-  using C = DCfg<T, D, DV, M, NA, PTW != 1>;
-  constexpr int PAD = C::PAD, W = C::W;
+  using C = DCfg<T, D, DV, M, NA, TB>;
+  constexpr int NW = C::NW, NT = C::NT, AW = C::AW, E = C::E, NS = D / F::KS;
+  const int NTOK = TB == 1 ? 1 : ntok;
   static_assert(C::BYTES <= 160 * 1024, "decode LDS budget");
   __shared__ __align__(16) char smem[C::BYTES];
-  T* sOm = (T*)(smem + C::oOm);
-  T* sRr = (T*)(smem + C::oRr);
-  T* sUt = (T*)(smem + C::oUt);
+  T* sR = (T*)(smem + C::oR);
+  T* sU = (T*)(smem + C::oU);
   float* sq = (float*)(smem + C::oQ);
   float* sk = (float*)(smem + C::oK);
   float* sv = (float*)(smem + C::oV);
-  float* schi = (float*)(smem + C::oChi);
-  float* san = (float*)(smem + C::oAn);
-  float* snz = (float*)(smem + C::oNz);
-  float* sred = (float*)(smem + C::oRed);
+  float* sNz = (float*)(smem + C::oNz);
   float* sN = (float*)(smem + C::oN);
+  float* sZ = (float*)(smem + C::oZ);
 
   const int tid = threadIdx.x, l = tid & 63, col = l & 31, h = l >> 5, wv = uniform(tid >> 6);
-  const int sh = blockIdx.x, H = A.H, w = A.w;
-  const int s = sh / H, hh = sh % H;
-  const int64_t t = A.pos[s];
-  const int slot = (int)(t % w);
-  const int nvalid = (int)((t + 1 < w) ? t + 1 : w);
-  const T* qt = (const T*)A.q + (size_t)sh * D;
-  const T* kt = (const T*)A.k + (size_t)sh * D;
-  const T* vt = (const T*)A.v + (size_t)sh * DV;
-  const T* rt = (const T*)A.r + (size_t)sh * D;
-  const T* ut = (const T*)A.u + (size_t)sh * DV;
-  T* rr = (T*)A.ring_r + (size_t)sh * w * D;
-  T* ru = (T*)A.ring_u + (size_t)sh * w * DV;
-  const float* om = A.omega + (size_t)hh * M * D;
-  float* Ms = A.M + (size_t)sh * M * DV;
-  float* as = A.a + (size_t)sh * M;
-
-  // The state rows this thread updates (feature tile pt = wv when each wave
-  // owns one tile) and its entry of a are fetched first: their latency then
-  // overlaps the staging, the key features and the logits.
-  constexpr bool PRE = PTW == 1;
-  float mreg[PRE ? DV / 32 : 1][16];
-  const float a_old = tid < M ? as[tid] : 0.0f;
-
-  // ---- the Omega rows of the key GEMV (m <= 128), then the token and both
-  // rings (slot t mod w replaced by the new token): every load is issued before
-  // the first LDS store, the bank's L2 latency under the staging's HBM loads
-  // (one memory round trip); slots from nvalid on hold no token yet and are
-  // staged as zero rows ----
-  static_assert(D <= 256 && DV <= 256, "one element of a token row per thread");
-  KeyBankRows<T, D> kb;
-  if constexpr (PRE) kb.load(om, M, tid);
-  RingStage<T, W, D, false> rgr;
-  RingStage<T, W, DV, true> rgu;
-  rgr.load(rr, rt, slot, w, tid);
-  rgu.load(ru, ut, slot, w, tid);
-  // (r_t and u_t are kept for the ring slot written at the end)
-  const T xq = qt[min(tid, D - 1)], xk = kt[min(tid, D - 1)], xv = vt[min(tid, DV - 1)];
-  const T xr = rt[min(tid, D - 1)], xu = ut[min(tid, DV - 1)];
-  const float Rold = A.rho[sh];
-  if (tid < D) {
-    sq[tid] = tof(xq);
-    sk[tid] = tof(xk);
-  }
-  if (tid < DV) sv[tid] = tof(xv);
-  rgr.store(sRr, D + PAD, nvalid, tid);
-  rgu.store(sUt, W + PAD, nvalid, tid);
-  if constexpr (!PRE) stage_omega<T, D, M>(sOm, om, tid);
-  // the state rows this thread updates, issued once the staging has been
-  // waited for: the memory counter drains in issue order, so no wait before
-  // the update includes them, and they arrive under the GEMV, the logits and
-  // the exponentials
-  if constexpr (PRE) {
-    if (wv < PT) {
-#pragma unroll
-      for (int dt = 0; dt < DV / 32; ++dt)
-#pragma unroll
-        for (int vv = 0; vv < 16; ++vv) mreg[dt][vv] = Ms[(size_t)(wv * 32 + crow(vv, h)) * DV + dt * 32 + col];
-    }
-  }
-  __syncthreads();
-
-  // ---- key features of k_t (float32 GEMV) and the frame update; with one
-  // feature tile per wave the Omega rows of the GEMV also give the logits'
-  // operand fragments (no LDS copy of the bank) ----
-  typename F::frag omf[PRE ? D / F::KS : 1];
-  float rho_t;
-  if constexpr (PRE) rho_t = key_log2_features_rows<T, D, M, PRE>(kb, sk, schi, sred, omf);
-  else rho_t = key_log2_features<T, D, M, PRE>(sk, om, schi, sred, omf);
-  const float lam = tid < M ? schi[tid] : kNegInf;   // each thread rewrites only its own entry below
-  const float Rn = fmaxf(Rold, rho_t);
-  const float sa = fast_exp2(Rold - Rn);          // 0 for an empty state (R = -inf)
-  if (tid < M) {
-    float chi = fast_exp2(lam - Rn) * rsqrtf((float)M);
-    schi[tid] = chi;
-    float an = sa * a_old + chi;
-    san[tid] = an;
-    as[tid] = an;
-  }
-  // ---- composite-query logits, lanes <-> feature p, registers <-> anchor ----
-  f32x16 acc[PTW][NA];
-  float nz[NA];
-#pragma unroll
-  for (int pi = 0; pi < PTW; ++pi)
-#pragma unroll
-    for (int ct = 0; ct < NA; ++ct) acc[pi][ct] = zero16();
-#pragma unroll
-  for (int ct = 0; ct < NA; ++ct) nz[ct] = 0.0f;
-  // (anchors past nvalid read zero ring rows, so z = 0 there without a mask)
-#pragma unroll
-  for (int ct = 0; ct < NA; ++ct) {
-    const int c = ct * 32 + col;
-    const bool valid = c < nvalid;
-#pragma unroll
-    for (int ks = 0; ks < D / F::KS; ++ks) {
-      no_hoist();                                 // the step's q reads stay in the step
-      const int k0 = ks * F::KS + h * F::KPL;
-      typename F::frag rf = F::ld(sRr + c * (D + PAD), k0), zf;
-      composite_query<T>(sq + k0, rf, nz[ct], zf);
-      if constexpr (PRE) {
-        if (wv < PT) acc[0][ct] = F::mma(zf, omf[ks], acc[0][ct]);
-      } else {
-#pragma unroll
-        for (int pi = 0; pi < PTW; ++pi) {
-          const int pt = wv + 4 * pi;
-          if (pt < PT)
-            acc[pi][ct] = F::mma(zf, F::ld(sOm + (pt * 32 + col) * (D + PAD), k0), acc[pi][ct]);
-        }
-      }
-    }
-    nz[ct] = half_swap_add(nz[ct]);
-    if (wv == 0 && h == 0) snz[c] = valid ? -0.5f * kLog2e * nz[ct] : kNegInf;
-  }
-  __syncthreads();
-  // row maximum over valid (anchor, feature)
-  float tm = kNegInf;
-#pragma unroll
-  for (int pi = 0; pi < PTW; ++pi) {
-    if (wv + 4 * pi >= PT) continue;
-#pragma unroll
-    for (int ct = 0; ct < NA; ++ct)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        float x = acc[pi][ct][v] + snz[ct * 32 + crow(v, h)];
-        acc[pi][ct][v] = x;
-        tm = fmaxf(tm, x);
-      }
-  }
-  tm = wave_max(tm);
-  if (l == 0) sred[8 + wv] = tm;
-  __syncthreads();
-  const float L = fmaxf(fmaxf(sred[8], sred[9]), fmaxf(sred[10], sred[11]));
-  // psi, Z, then W = Psi^T U and N = sum_p M'[p,:] (*) W[p,:] with the state update
-  float zpart = 0.0f;
-  float npart[DV / 32];
-#pragma unroll
-  for (int dt = 0; dt < DV / 32; ++dt) npart[dt] = 0.0f;
-#pragma unroll
-  for (int pi = 0; pi < PTW; ++pi) {
-    const int pt = wv + 4 * pi;
-    if (pt >= PT) continue;
-    const float anp = san[pt * 32 + col];
-#pragma unroll
-    for (int ct = 0; ct < NA; ++ct)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        float psi = fast_exp2(acc[pi][ct][v] - L);
-        acc[pi][ct][v] = psi;
-        zpart += psi * anp;
-      }
-#pragma unroll
-    for (int dt = 0; dt < DV / 32; ++dt) {
-      no_hoist();
-      f32x16 accW = zero16();
-      const T* urow = sUt + (dt * 32 + col) * (W + PAD);
-#pragma unroll
-      for (int ct = 0; ct < NA; ++ct)
-#pragma unroll
-        for (int sp = 0; sp < F::CSTEPS; ++sp)
-          accW = F::mma(F::cfrag(acc[pi][ct], sp), F::ldc(urow, ct * 32, sp, h), accW);
-      // accW: lanes <-> d, registers <-> p
-      const int d = dt * 32 + col;
-      const float vd = sv[d];
-      float np = 0.0f;
-#pragma unroll
-      for (int vv = 0; vv < 16; ++vv) {
-        const int p = pt * 32 + crow(vv, h);
-        float* mp = Ms + (size_t)p * DV + d;
-        float mold;
-        if constexpr (PRE) mold = mreg[dt][vv];
-        else mold = *mp;
-        float mnew = sa * mold + schi[p] * vd;
-        *mp = mnew;
-        np += mnew * accW[vv];
-      }
-      npart[dt] += np;
-    }
-  }
-  // (feature tile pt belongs to wave pt mod 4, so every state row is updated once)
-  zpart = wave_sum(zpart);
-  if (l == 0) sred[16 + wv] = zpart;
-#pragma unroll
-  for (int dt = 0; dt < DV / 32; ++dt) {
-    float nn = half_swap_add(npart[dt]);
-    if (h == 0) sN[wv * DV + dt * 32 + col] = nn;
-  }
-  __syncthreads();
-  const float Z = (sred[16] + sred[17]) + (sred[18] + sred[19]);
-  const float inv = 1.0f / (Z + A.eps);
-  for (int d = tid; d < DV; d += 256) {
-    float N = (sN[d] + sN[DV + d]) + (sN[2 * DV + d] + sN[3 * DV + d]);
-    ((T*)A.out)[(size_t)sh * DV + d] = (T)(N * inv);
-  }
-  // ring slot and frame
-  if (tid < D) rr[(size_t)slot * D + tid] = xr;
-  if (tid < DV) ru[(size_t)slot * DV + tid] = xu;
-  if (tid == 0) A.rho[sh] = Rn;
-}
-
-// ---------------------------------------------------------------------------
-// Chunked decode: NT tokens per sequence in one launch (token j of sequence s
-// is position pos[s] + j).  The same per-token step as k_decode, but the
-// state stays on chip for the whole chunk: the ring anchors live in LDS and
-// are overwritten slot by slot, a lives in the registers of the threads that
-// own a feature, and M (for m <= 128) lives in the registers of the threads
-// that update it, so each state element is read and written once per chunk
-// instead of once per token.  For m = 256 M is streamed through global memory
-// per token as in k_decode.
-// ---------------------------------------------------------------------------
-template <typename T, int D, int DV, int M, int NA>
-__global__ __launch_bounds__(256) void k_decode_chunk(DecArgs A, int NTOK) {
-  using F = MF<T>;
-  using C = DCfg<T, D, DV, M, NA>;
-  constexpr int PAD = C::PAD, W = C::W;
-  constexpr int PT = M / 32;                  // feature tiles
-  constexpr int PTW = (PT + 3) / 4;           // feature tiles per wave
-  constexpr bool RES = PTW == 1;              // M held in registers across the chunk
-  static_assert(C::BYTES <= 160 * 1024, "decode LDS budget");
-  __shared__ __align__(16) char smem[C::BYTES];
-  T* sOm = (T*)(smem + C::oOm);
-  T* sRr = (T*)(smem + C::oRr);
-  T* sUt = (T*)(smem + C::oUt);
-  float* sq = (float*)(smem + C::oQ);
-  float* sk = (float*)(smem + C::oK);
-  float* sv = (float*)(smem + C::oV);
-  float* schi = (float*)(smem + C::oChi);
-  float* san = (float*)(smem + C::oAn);
-  float* snz = (float*)(smem + C::oNz);
-  float* sred = (float*)(smem + C::oRed);
-  float* sN = (float*)(smem + C::oN);
-
-  const int tid = threadIdx.x, l = tid & 63, col = l & 31, h = l >> 5, wv = uniform(tid >> 6);
+  float* schi = (float*)(smem + C::oChi) + wv * 32;
+  float* slam = (float*)(smem + C::oLam) + wv * TB * 32;
   const int sh = blockIdx.x, H = A.H, w = A.w;
   const int s = sh / H, hh = sh % H;
   const int64_t t0 = A.pos[s];
+  const int told = (int)(t0 < AW ? t0 : AW);                   // tokens before the call that can be anchors
+  const int slot0 = (int)(t0 % w);                             // ring slot of the call's first token
   T* rr = (T*)A.ring_r + (size_t)sh * w * D;
   T* ru = (T*)A.ring_u + (size_t)sh * w * DV;
-  const float* om = A.omega + (size_t)hh * M * D;
+  const size_t tok0 = (size_t)sh * NTOK;
+  const T *rg = (const T*)A.r + tok0 * D, *ug = (const T*)A.u + tok0 * DV;
   float* Ms = A.M + (size_t)sh * M * DV;
   float* as = A.a + (size_t)sh * M;
 
-  // ring, Omega and the state, once per chunk; while t0 < w the slots t0 .. w-1
-  // hold no token yet: they are staged as zero rows and the chunk's tokens
-  // fill them in order
-  const int nv0 = (int)(t0 < w ? t0 : w);
-  {
-    RingStage<T, W, D, false> rgr;
-    RingStage<T, W, DV, true> rgu;
-    rgr.load(rr, nullptr, 0, w, tid);
-    rgu.load(ru, nullptr, 0, w, tid);
-    rgr.store(sRr, D + PAD, nv0, tid);
-    rgu.store(sUt, W + PAD, nv0, tid);
-  }
-  stage_omega<T, D, M>(sOm, om, tid);
-  float areg = (tid < M) ? as[tid] : 0.0f;
-  float R = A.rho[sh];
-  float Mreg[RES ? DV / 32 : 1][16];
-  if constexpr (RES) {
-    if (wv < PT) {
+  // LDS row of token i of the call, i >= -AW (i < 0: before the call)
+  auto row_of = [](int i) { return (i + AW) % E; };
+  constexpr int VE = 16 / (int)sizeof(T);
+  typedef T V __attribute__((ext_vector_type(VE)));
+  // a block's token rows: q, k, v as float32, r and u into the ring
+  static_assert(D == DV && (NT & (NT - 1)) == 0, "rows of one width, thread mask");
+  constexpr int PD = D / VE, PT = 5 * PD, NP = TB * PT, PIT = (NP + NT - 1) / NT;
+  // (thread numbers made opaque where a block or a token starts: the addresses
+  // are formed there instead of being held in registers across the loops)
+  auto opaque = [](int x, int mask) { asm volatile("" : "+v"(x)); return x & mask; };
+  // one piece into an LDS row (float32 rows are padded by one element: not 16-byte aligned)
+  auto put = [](T* dst, const V& x) {
+    if constexpr (sizeof(T) == 2) *(V*)dst = x;
+    else {
 #pragma unroll
-      for (int dt = 0; dt < DV / 32; ++dt)
-#pragma unroll
-        for (int vv = 0; vv < 16; ++vv) Mreg[dt][vv] = Ms[(size_t)(wv * 32 + crow(vv, h)) * DV + dt * 32 + col];
+      for (int e = 0; e < VE; ++e) dst[e] = x[e];
     }
-  }
-
-  // a token's q, k, r (element tid of D) and v, u (element tid of DV) are
-  // loaded one token ahead into registers: their latency then overlaps the
-  // previous token's work instead of opening each token's chain.  Every
-  // thread loads (index clamped into the row), so no load sits under a branch.
-  static_assert(D <= 256 && DV <= 256, "one element of a token row per thread");
-  const int iD = min(tid, D - 1), iV = min(tid, DV - 1);
-  T xq, xk, xr, xv, xu;
-  auto fetch_token = [&](int j) {
-    const size_t tok = (size_t)sh * NTOK + j;
-    xq = ((const T*)A.q)[tok * D + iD];
-    xk = ((const T*)A.k)[tok * D + iD];
-    xr = ((const T*)A.r)[tok * D + iD];
-    xv = ((const T*)A.v)[tok * DV + iV];
-    xu = ((const T*)A.u)[tok * DV + iV];
   };
-  fetch_token(0);
+  V xt[PIT];
+  auto fetch = [&](int j0) {
+    const int tid = opaque(threadIdx.x, NT - 1);
+#pragma unroll
+    for (int it = 0; it < PIT; ++it) {
+      const int idx = min(tid + NT * it, NP - 1), j = min(j0 + idx / PT, NTOK - 1), ti = idx % PT / PD, c = idx % PD;
+      uintptr_t p = (uintptr_t)A.q;
+      p = ti == 1 ? (uintptr_t)A.k : p;
+      p = ti == 2 ? (uintptr_t)A.v : p;
+      p = ti == 3 ? (uintptr_t)A.r : p;
+      p = ti == 4 ? (uintptr_t)A.u : p;
+      xt[it] = *(const V*)((const T*)p + (tok0 + j) * D + c * VE);
+    }
+  };
+  auto place = [&](int j0) {
+    const int tid = opaque(threadIdx.x, NT - 1);
+#pragma unroll
+    for (int it = 0; it < PIT; ++it) {
+      const int idx = tid + NT * it, jj = idx / PT, ti = idx % PT / PD, c = idx % PD;
+      if (NP % NT != 0 && idx >= NP) continue;
+      if (ti < 3) {
+        float* dst = sq + (ti * TB + jj) * D + c * VE;         // q, k, v lie one after the other
+#pragma unroll
+        for (int e = 0; e < VE; ++e) dst[e] = tof(xt[it][e]);
+      } else {
+        const int row = row_of(j0 + jj);
+        put((ti == 3 ? sR + row * C::RST : sU + row * C::UST) + c * VE, xt[it]);
+      }
+    }
+  };
+  // The loads of the prologue in the order they are waited for: the first
+  // block's tokens, the ring and the bank, staged, then the state, which arrives
+  // under the key features and the logits (the memory counter drains in order).
+  fetch(0);
+  // ---- this wave's bank rows (Omega log2 e, lanes <-> p, the operand's pieces of D) ----
+  float om[NS][F::KPL];
+  {
+    const float* orow = A.omega + ((size_t)hh * M + wv * 32 + col) * D + h * F::KPL;
+#pragma unroll
+    for (int ks = 0; ks < NS; ++ks)
+#pragma unroll
+      for (int e = 0; e < F::KPL; ++e) om[ks][e] = orow[ks * F::KS + e] * kLog2e;
+  }
+  // ---- anchors before the call: tokens -(AW - 1) .. -1 from the ring slots
+  // (t0 + i) mod w, zero rows where the window or the sequence ends ----
+  {
+    constexpr int PR = D / VE, PW = PR + DV / VE, N = (AW - 1) * PW, IT = (N + NT - 1) / NT;
+    V x[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int idx = min(tid + NT * it, N - 1), back = idx / PW + 1, c = idx % PW;
+      const int slot = slot0 - min(back, w);                   // (rows past the window or the sequence: dropped below)
+      const int sl = slot < 0 ? slot + w : slot;
+      x[it] = *(const V*)(c < PR ? rr + (size_t)sl * D + c * VE : ru + (size_t)sl * DV + (c - PR) * VE);
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int idx = tid + NT * it, back = idx / PW + 1, c = idx % PW;
+      if (N % NT != 0 && idx >= N) continue;
+      const bool ok = back < w && back <= told;
+      const V zero = {};
+      put(c < PR ? sR + row_of(-back) * C::RST + c * VE : sU + row_of(-back) * C::UST + (c - PR) * VE, ok ? x[it] : zero);
+    }
+    // the one row no token of the first block's windows has yet
+    for (int e = tid; e < D; e += NT) sR[row_of(-AW) * C::RST + e] = (T)0.0f;
+    for (int e = tid; e < DV; e += NT) sU[row_of(-AW) * C::UST + e] = (T)0.0f;
+    place(0);
+  }
+  // ---- this wave's rows of M and entries of a ----
+  float Mreg[DV / 32][16];
+#pragma unroll
+  for (int dt = 0; dt < DV / 32; ++dt)
+#pragma unroll
+    for (int vv = 0; vv < 16; ++vv) Mreg[dt][vv] = Ms[(size_t)(wv * 32 + crow(vv, h)) * DV + dt * 32 + col];
+  float areg = as[wv * 32 + col];
+  float R = A.rho[sh];
 
 #pragma unroll 1
-  for (int j = 0; j < NTOK; ++j) {
-    const int64_t t = t0 + j;
-    const int slot = (int)(t % w);
-    const int nvalid = (int)((t + 1 < w) ? t + 1 : w);
-    const size_t tok = (size_t)sh * NTOK + j;
-    __syncthreads();                              // the previous token is done with LDS
-    if (tid < D) {
-      sq[tid] = tof(xq);
-      sk[tid] = tof(xk);
-      sRr[slot * (D + PAD) + tid] = xr;
+  for (int j0 = 0; j0 < NTOK; j0 += TB) {
+    const int nb = TB == 1 ? 1 : min(TB, NTOK - j0);
+    __syncthreads();
+    // ---- |z|^2 of the block's (token, anchor) pairs in float32: TPA threads an
+    // anchor, each every TPA-th 16-byte piece of the row, their sums added in order ----
+    {
+      constexpr int TPA = NT >= AW ? (NT / AW >= 4 ? 4 : NT / AW >= 2 ? 2 : 1) : 1, APP = NT / TPA;
+      const int tid = opaque(threadIdx.x, NT - 1), part = tid % TPA;
+#pragma unroll 1
+      for (int idx = tid / TPA; idx < nb * AW; idx += APP) {
+        const int j = idx / AW, dl = idx % AW, i = j0 + j;
+        const int rrow = row_of(i) - dl;
+        const T* rp = sR + (rrow < 0 ? rrow + E : rrow) * C::RST;
+        const float* qp = sq + j * D;
+        float x = 0.0f;
+#pragma unroll
+        for (int c = 0; c < D / VE / TPA; ++c) {
+          const int e0 = (c * TPA + part) * VE;
+#pragma unroll
+          for (int e = 0; e < VE; ++e) {
+            const float z = qp[e0 + e] * tof(rp[e0 + e]);
+            x = __builtin_fmaf(z, z, x);
+          }
+        }
+        if constexpr (TPA >= 2) x += dpp<0xB1>(x);             // quad_perm [1,0,3,2]
+        if constexpr (TPA >= 4) x += dpp<0x4E>(x);             // quad_perm [2,3,0,1]
+        if (part == 0) sNz[idx] = dl < w && t0 + i - dl >= 0 ? -0.5f * kLog2e * x : kNegInf;
+      }
     }
-    if (tid < DV) {
-      sv[tid] = tof(xv);
-      sUt[tid * (W + PAD) + F::sigma(slot)] = xu;
+    // ---- key log2-features of the block's tokens (float32) and their maxima ----
+#pragma unroll 1
+    for (int j = 0; j < nb; ++j) {
+      const int l = opaque(lane_id(), 63), col = l & 31, h = l >> 5;
+      const float* kr = sk + j * D;
+      float nk = 0.0f, lam = 0.0f;
+#pragma unroll
+      for (int e = l; e < D; e += 64) nk = __builtin_fmaf(kr[e], kr[e], nk);
+      nk = wave_sum(nk);
+#pragma unroll
+      for (int ks = 0; ks < NS; ++ks) {
+        if (ks % 4 == 0) no_hoist();                           // a few reads in flight, not all of the row
+#pragma unroll
+        for (int e = 0; e < F::KPL; ++e) lam = __builtin_fmaf(om[ks][e], kr[ks * F::KS + h * F::KPL + e], lam);
+      }
+      lam = __builtin_fmaf(-0.5f * kLog2e, nk, half_swap_add(lam));
+      const float mx = wave_max(lam);
+      if (h == 0) slam[j * 32 + col] = lam;
+      if (l == 0) sZ[3 * (wv * TB + j) + 2] = mx;
     }
     __syncthreads();
 
-    // key features of k_t and the frame update
-    const float rho_t = key_log2_features<T, D, M, false>(sk, om, schi, sred, nullptr);
-    // the next token's rows, issued after the bank loads of the key GEMV (the
-    // memory counter drains in issue order: issued before them, they would be
-    // waited for with them)
-    if (j + 1 < NTOK) fetch_token(j + 1);
-    const float lam = tid < M ? schi[tid] : kNegInf;
-    const float Rn = fmaxf(R, rho_t);
-    const float sa = fast_exp2(R - Rn);
-    if (tid < M) {
-      const float chi = fast_exp2(lam - Rn) * rsqrtf((float)M);
-      schi[tid] = chi;
-      areg = sa * areg + chi;
-      san[tid] = areg;
-    }
-    // composite-query logits (lanes <-> feature, registers <-> anchor)
-    f32x16 acc[PTW][NA];
-    float nz[NA];
+#pragma unroll 1
+    for (int j = 0; j < nb; ++j) {
+      const int l = opaque(lane_id(), 63), col = l & 31, h = l >> 5;
+      // ---- the frame, chi and a ----
+      float Rn = R;
 #pragma unroll
-    for (int pi = 0; pi < PTW; ++pi)
+      for (int ww = 0; ww < NW; ++ww) Rn = fmaxf(Rn, sZ[3 * (ww * TB + j) + 2]);
+      Rn = uniform(Rn);
+      const float sa = uniform(fast_exp2(R - Rn));             // 0 for an empty state (R = -inf)
+      const float chi = fast_exp2(slam[j * 32 + col] - Rn) * rsqrtf((float)M);
+      areg = __builtin_fmaf(sa, areg, chi);
+      R = Rn;
+      if (h == 0) schi[col] = chi;
+      if (sa != 1.0f) {
 #pragma unroll
-      for (int ct = 0; ct < NA; ++ct) acc[pi][ct] = zero16();
+        for (int dt = 0; dt < DV / 32; ++dt)
 #pragma unroll
-    for (int ct = 0; ct < NA; ++ct) nz[ct] = 0.0f;
+          for (int vv = 0; vv < 16; ++vv) Mreg[dt][vv] *= sa;
+      }
+      // ---- logits (registers <-> anchor offset, lanes <-> p) ----
+      const int ib = row_of(j0 + j);
+      auto ring_row = [&](int dl) { const int e = ib - dl; return e < 0 ? e + E : e; };   // dl <= AW - 1 < E
+      const float* qr = sq + j * D;
+      const T* arow[NA];
 #pragma unroll
-    for (int ct = 0; ct < NA; ++ct) {
-      const int c = ct * 32 + col;
-      const bool valid = c < nvalid;
-#pragma unroll 2
-      for (int ks = 0; ks < D / F::KS; ++ks) {
-        no_hoist();
+      for (int an = 0; an < NA; ++an) arow[an] = sR + ring_row(32 * an + col) * C::RST;
+      f32x16 acc[NA];
+#pragma unroll
+      for (int an = 0; an < NA; ++an) acc[an] = zero16();
+#pragma unroll
+      for (int ks = 0; ks < NS; ++ks) {
+        if (ks % 2 == 0) no_hoist();
         const int k0 = ks * F::KS + h * F::KPL;
-        typename F::frag rf = F::ld(sRr + c * (D + PAD), k0), zf;
-        composite_query<T>(sq + k0, rf, nz[ct], zf);
+        typename F::frag b;
+        if constexpr (sizeof(T) == 2) {
+          const f32x4 q0 = *(const f32x4*)(qr + k0), q1 = *(const f32x4*)(qr + k0 + 4);
 #pragma unroll
-        for (int pi = 0; pi < PTW; ++pi) {
-          const int pt = wv + 4 * pi;
-          if (pt < PT)
-            acc[pi][ct] = F::mma(zf, F::ld(sOm + (pt * 32 + col) * (D + PAD), k0), acc[pi][ct]);
+          for (int e = 0; e < 8; ++e) b[e] = (bf16)(om[ks][e] * (e < 4 ? q0[e] : q1[e - 4]));
+        } else {
+          b = om[ks][0] * qr[k0];
+        }
+#pragma unroll
+        for (int an = 0; an < NA; ++an) acc[an] = F::mma(F::ld(arow[an], k0), b, acc[an]);
+      }
+      float tm = kNegInf;
+#pragma unroll
+      for (int an = 0; an < NA; ++an) {
+        float bias[16];
+        crow_vals(sNz + j * AW + 32 * an, bias);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          acc[an][v] += bias[v];
+          tm = fmaxf(tm, acc[an][v]);
         }
       }
-      nz[ct] = half_swap_add(nz[ct]);
-      if (wv == 0 && h == 0) snz[c] = valid ? -0.5f * kLog2e * nz[ct] : kNegInf;
-    }
-    __syncthreads();
-    float tm = kNegInf;
+      const float L = wave_max(tm);
+      float ps = 0.0f;
+      typename F::frag pf[NA][F::CSTEPS];
 #pragma unroll
-    for (int pi = 0; pi < PTW; ++pi) {
-      if (wv + 4 * pi >= PT) continue;
-#pragma unroll
-      for (int ct = 0; ct < NA; ++ct)
+      for (int an = 0; an < NA; ++an) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const float x = acc[pi][ct][v] + snz[ct * 32 + crow(v, h)];
-          acc[pi][ct][v] = x;
-          tm = fmaxf(tm, x);
+          acc[an][v] = fast_exp2(acc[an][v] - L);
+          ps += acc[an][v];
         }
-    }
-    tm = wave_max(tm);
-    if (l == 0) sred[8 + wv] = tm;
-    __syncthreads();
-    const float L = fmaxf(fmaxf(sred[8], sred[9]), fmaxf(sred[10], sred[11]));
-    float zpart = 0.0f;
-    float npart[DV / 32];
 #pragma unroll
-    for (int dt = 0; dt < DV / 32; ++dt) npart[dt] = 0.0f;
-#pragma unroll
-    for (int pi = 0; pi < PTW; ++pi) {
-      const int pt = wv + 4 * pi;
-      if (pt >= PT) continue;
-      const float anp = san[pt * 32 + col];
-#pragma unroll
-      for (int ct = 0; ct < NA; ++ct)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float psi = fast_exp2(acc[pi][ct][v] - L);
-          acc[pi][ct][v] = psi;
-          zpart += psi * anp;
-        }
+        for (int sp = 0; sp < F::CSTEPS; ++sp) pf[an][sp] = F::cfrag(acc[an], sp);
+      }
+      const float zw = wave_sum(ps * areg);
+      // ---- W = Psi^T U, the state update and N = sum_p M (*) W (lanes <-> d, registers <-> p) ----
+      wave_lds_sync();                                         // chi
+      float cr[16];
+      crow_vals(schi, cr);
+      float* nrow = sN + (wv * TB + j) * DV;
 #pragma unroll
       for (int dt = 0; dt < DV / 32; ++dt) {
+        no_hoist();
         f32x16 accW = zero16();
-        const T* urow = sUt + (dt * 32 + col) * (W + PAD);
 #pragma unroll
-        for (int ct = 0; ct < NA; ++ct)
+        for (int an = 0; an < NA; ++an) {
+          auto rmap = [&](int ar) { return ring_row(32 * an + ar); };
 #pragma unroll
           for (int sp = 0; sp < F::CSTEPS; ++sp)
-            accW = F::mma(F::cfrag(acc[pi][ct], sp), F::ldc(urow, ct * 32, sp, h), accW);
-        const int d = dt * 32 + col;
-        const float vd = sv[d];
+            accW = F::mma(pf[an][sp], F::tld_crow_map(sU, C::UST, sp, dt * 32, rmap), accW);
+        }
+        const float vd = sv[j * DV + dt * 32 + col];
         float np = 0.0f;
 #pragma unroll
         for (int vv = 0; vv < 16; ++vv) {
-          const int p = pt * 32 + crow(vv, h);
-          float mnew;
-          if constexpr (RES) {
-            mnew = sa * Mreg[dt][vv] + schi[p] * vd;
-            Mreg[dt][vv] = mnew;
-          } else {
-            float* mp = Ms + (size_t)p * DV + d;
-            mnew = sa * (*mp) + schi[p] * vd;
-            *mp = mnew;
-          }
-          np += mnew * accW[vv];
+          Mreg[dt][vv] = __builtin_fmaf(cr[vv], vd, Mreg[dt][vv]);
+          np = __builtin_fmaf(Mreg[dt][vv], accW[vv], np);
         }
-        npart[dt] += np;
+        np = half_swap_add(np);
+        if (h == 0) nrow[dt * 32 + col] = np;
+      }
+      if (l == 0) {
+        float* z = sZ + 3 * (wv * TB + j);
+        z[0] = zw;
+        z[1] = L;
       }
     }
-    zpart = wave_sum(zpart);
-    if (l == 0) sred[16 + wv] = zpart;
-#pragma unroll
-    for (int dt = 0; dt < DV / 32; ++dt) {
-      const float nn = half_swap_add(npart[dt]);
-      if (h == 0) sN[wv * DV + dt * 32 + col] = nn;
-    }
+    const bool more = TB > 1 && j0 + TB < NTOK;
+    if (more) fetch(j0 + TB);
     __syncthreads();
-    const float Z = (sred[16] + sred[17]) + (sred[18] + sred[19]);
-    const float inv = 1.0f / (Z + A.eps);
-    for (int d = tid; d < DV; d += 256) {
-      const float N = (sN[d] + sN[DV + d]) + (sN[2 * DV + d] + sN[3 * DV + d]);
-      ((T*)A.out)[tok * DV + d] = (T)(N * inv);
+    if (more) place(j0 + TB);
+    // ---- outputs: the waves' parts at the largest row shift ----
+    for (int idx = tid; idx < nb * DV; idx += NT) {
+      const int j = idx / DV, d = idx % DV;
+      float Lm = kNegInf;
+#pragma unroll
+      for (int ww = 0; ww < NW; ++ww) Lm = fmaxf(Lm, sZ[3 * (ww * TB + j) + 1]);
+      float Z = 0.0f, N = 0.0f;
+#pragma unroll
+      for (int ww = 0; ww < NW; ++ww) {
+        const float* z = sZ + 3 * (ww * TB + j);
+        const float f = fast_exp2(z[1] - Lm);
+        Z = __builtin_fmaf(z[0], f, Z);
+        N = __builtin_fmaf(sN[(ww * TB + j) * DV + d], f, N);
+      }
+      ((T*)A.out)[(tok0 + j0 + j) * DV + d] = (T)(N / (Z + A.eps));
     }
-    R = Rn;
   }
 
-  // state and ring back to global memory
-  if constexpr (RES) {
-    if (wv < PT) {
+  // ---- state back ----
 #pragma unroll
-      for (int dt = 0; dt < DV / 32; ++dt)
+  for (int dt = 0; dt < DV / 32; ++dt)
 #pragma unroll
-        for (int vv = 0; vv < 16; ++vv) Ms[(size_t)(wv * 32 + crow(vv, h)) * DV + dt * 32 + col] = Mreg[dt][vv];
-    }
-  }
-  if (tid < M) as[tid] = areg;
+    for (int vv = 0; vv < 16; ++vv) Ms[(size_t)(wv * 32 + crow(vv, h)) * DV + dt * 32 + col] = Mreg[dt][vv];
+  if (h == 0) as[wv * 32 + col] = areg;
   if (tid == 0) A.rho[sh] = R;
-  // the last min(NTOK, w) tokens stay in the ring: their rows are read from the
-  // LDS ring (written by their tokens and made visible by the tokens' barriers),
-  // not again from global memory (a global load per row, each waited for)
-  const int jlo = NTOK > w ? NTOK - w : 0;
-  for (int j = jlo; j < NTOK; ++j) {
-    const int slot = (int)((t0 + j) % w);
-    for (int e = tid; e < D; e += 256) rr[(size_t)slot * D + e] = sRr[slot * (D + PAD) + e];
-    for (int e = tid; e < DV; e += 256) ru[(size_t)slot * DV + e] = sUt[e * (W + PAD) + F::sigma(slot)];
+  // the last min(NTOK, w) tokens into their ring slots
+  {
+    constexpr int PR = D / VE, PW = PR + DV / VE;
+    const int jlo = NTOK > w ? NTOK - w : 0, total = (NTOK - jlo) * PW;
+    for (int base = 0; base < total; base += 4 * NT) {
+      V x[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int idx = min(base + tid + NT * i, total - 1), j = jlo + idx / PW, c = idx % PW;
+        x[i] = *(const V*)(c < PR ? rg + (size_t)j * D + c * VE : ug + (size_t)j * DV + (c - PR) * VE);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int idx = base + tid + NT * i, j = jlo + idx / PW, c = idx % PW;
+        if (idx >= total) continue;
+        const int slot = (slot0 + j) % w;
+        *(V*)(c < PR ? rr + (size_t)slot * D + c * VE : ru + (size_t)slot * DV + (c - PR) * VE) = x[i];
+      }
+    }
   }
 }
 
@@ -733,12 +415,13 @@ template <typename T, int D, int DV, int M, int NA>
 static int run_decode(int64_t S, DecArgs a, int ntok, hipStream_t st) {
   // the caller bounds S*H by kMaxDecodeGroups (one workgroup each)
   (void)hipGetLastError();                             // an earlier call's error is not this one's
+  const unsigned groups = (unsigned)(S * a.H);
   if (ntok == 1) {
     ProfScope ps("decode", st);
-    k_decode<T, D, DV, M, NA><<<(unsigned)(S * a.H), 256, 0, st>>>(a);
+    k_decode<T, D, DV, M, NA, 1><<<groups, DCfg<T, D, DV, M, NA, 1>::NT, 0, st>>>(a, ntok);
   } else {
     ProfScope ps("decode_chunk", st);
-    k_decode_chunk<T, D, DV, M, NA><<<(unsigned)(S * a.H), 256, 0, st>>>(a, ntok);
+    k_decode<T, D, DV, M, NA, 8><<<groups, DCfg<T, D, DV, M, NA, 8>::NT, 0, st>>>(a, ntok);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {                               // pos must not advance past a step not taken

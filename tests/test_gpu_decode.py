@@ -278,3 +278,17 @@ def test_prefill_state(D, m, n, w, S, H, dt):
             assert abs(float(st["rho"][s, h]) - lam) <= 1e-3
             assert np.array_equal(f64(st["ring_r"][s, h]), ref["ring_r"])
             assert np.array_equal(f64(st["ring_u"][s, h]), ref["ring_u"])
+
+
+@pytest.mark.parametrize("dtype,D,m,w,P,T", [
+    ("bf16", 128, 128, 64, 70, 8),      # one whole block of tokens
+    ("bf16", 128, 128, 1, 5, 9),        # a block and a token; one anchor a row
+    ("bf16", 128, 256, 32, 20, 17),     # eight waves, one anchor tile
+    ("bf16", 32, 32, 128, 100, 33),     # one wave, four anchor tiles, the window fills on the way
+    ("bf16", 128, 64, 65, 0, 24),       # empty state, a window just over two tiles
+    ("f32", 64, 64, 33, 40, 16),
+    ("f32", 64, 32, 96, 3, 10),
+    ("f32", 32, 64, 64, 64, 2),
+])
+def test_decode_chunk_block_edges(dtype, D, m, w, P, T):
+    test_decode_chunk_matches_steps_and_forward(dtype, D, m, w, P, T)
