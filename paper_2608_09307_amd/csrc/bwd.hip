@@ -1572,15 +1572,6 @@ static int launch_err(const char* what) {
   return 0;
 }
 
-// Workgroups of a kernel that run at once on the chip (256 CUs)
-template <typename K>
-static int64_t kernel_slots(K kernel, int threads) {
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kernel, threads, 0) != hipSuccess) per_cu = 0;
-  (void)hipGetLastError();
-  return 256 * (int64_t)(per_cu > 0 ? per_cu : 1);
-}
-
 // Chunks per workgroup of the state sweep (1, 2, 4 or 8).  A segment of several
 // chunks leaves one state gradient where each chunk left its own (written by
 // the sweep, read and written by the reverse scan, read twice by the key side:

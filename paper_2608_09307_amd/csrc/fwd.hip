@@ -549,7 +549,7 @@ __global__ __launch_bounds__(64 * NW) void k_readout(FwdArgs a) {
   const bool has_bnd = cb > 0;
 
   // ---- prologue ----
-  const int fbk = blockIdx.z;
+  const int fbk = blockIdx.z % C::NFB;
   {
     // every global load of the prologue first, then the LDS stores; the
     // transposed copies take the row index fastest across lanes, so the
@@ -631,9 +631,10 @@ __global__ __launch_bounds__(64 * NW) void k_readout(FwdArgs a) {
   }
   __syncthreads();
 
-  const int fb = blockIdx.z;       // feature block handled by this workgroup
+  const int fb = fbk;              // feature block handled by this workgroup
+  // the chunk's rows, by gridDim.z / NFB workgroups (more than one for small grids)
 #pragma unroll 1
-  for (int rr = 0; rr < RPW; ++rr) {
+  for (int rr = blockIdx.z / C::NFB; rr < RPW; rr += gridDim.z / C::NFB) {
     const int t = wv + NW * rr;
     const int i = s0 + t;
     if (t >= C::BC || i >= n) continue;
@@ -928,9 +929,15 @@ static int run_fwd(const Shape& s, FwdArgs a, hipStream_t st) {
   { ProfScope ps("keyfeat", st);
   k_keyfeat<T, D, M><<<dim3((nch + 3) / 4, BH), 256, 0, st>>>(a); }
   if (a.out != nullptr) {
-    constexpr int NFB = RCfg<T, D, DV, M, NW, NA>::NFB;
+    using R = RCfg<T, D, DV, M, NW, NA>;
+    constexpr int NFB = R::NFB;
+    // a grid that leaves CUs idle gives each round of a chunk's rows a workgroup
+    // of its own (it stages the chunk's window again, beside the others): one
+    // float32 head of 256 tokens, 8 chunks, 44 -> 21 us
+    static const int64_t slots = kernel_slots(k_readout<T, D, DV, M, NW, NA>, 64 * NW);
+    const int parts = (int64_t)nch * BH * NFB * R::RPW <= slots ? R::RPW : 1;
     { ProfScope ps("fwd_readout", st);
-    k_readout<T, D, DV, M, NW, NA><<<dim3(nch, BH, NFB), 64 * NW, 0, st>>>(a); }
+    k_readout<T, D, DV, M, NW, NA><<<dim3(nch, BH, NFB * parts), 64 * NW, 0, st>>>(a); }
     if constexpr (NFB > 1) {
       ProfScope ps("fwd_merge", st);
       size_t rows = (size_t)BH * s.n;

@@ -103,6 +103,15 @@ int launch_feature_bank(int H, int m, int D, const float* gauss, const float* ra
 // a one-dimensional grid (fewer than 2^32 threads)
 constexpr int64_t kMaxDecodeGroups = ((int64_t)1 << 24) - 1;
 
+// Workgroups of a kernel that run at once on the chip (256 CUs)
+template <typename K>
+inline int64_t kernel_slots(K kernel, int threads) {
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kernel, threads, 0) != hipSuccess) per_cu = 0;
+  (void)hipGetLastError();
+  return 256 * (int64_t)(per_cu > 0 ? per_cu : 1);
+}
+
 void set_error(const char* fmt, ...);
 bool shape_supported(const Shape& s, bool backward);
 
