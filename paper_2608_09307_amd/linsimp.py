@@ -128,32 +128,43 @@ def _ptr(t: Optional[torch.Tensor], name: str):
         raise ValueError(f"{name} must be a GPU tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the raw handle, without the Stream object torch.cuda.current_stream builds
+    # (4 us of a 21 us decode step's host time)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
-def _expect(pairs, device=None):
+def _expect(pairs):
     """Check (tensor, name, shape, dtype) tuples before their pointers go to
     the C ABI, which sees bare pointers and trusts the sizes it is given: a
     tensor of the wrong shape would be read or written out of bounds.  Shape
-    and dtype are checked first, then that every tensor is on the first one's
-    device and that this is the current device (the launch stream's)."""
+    and dtype are checked first, then that every tensor is dense, on a GPU, on
+    the first one's device, and that this is the current device (the launch
+    stream's).  Returns the tensors' addresses, in order."""
     for t, name, shape, dtype in pairs:
         if t is None:
             raise ValueError(f"{name} is required")
-        if tuple(t.shape) != tuple(shape):
+        if t.shape != shape:
             raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
         if t.dtype != dtype:
             raise TypeError(f"{name} has dtype {t.dtype}, expected {dtype}")
-    dev = device if device is not None else pairs[0][0].device
+    first = pairs[0][0]
+    idx = first.get_device()                          # -1: not a GPU
+    ptrs = []
     for t, name, _, _ in pairs:
-        if t.device != dev:
-            raise ValueError(f"{name} is on {t.device}, expected {dev}")
-    if dev.type == "cuda" and dev.index is not None and dev.index != torch.cuda.current_device():
-        raise ValueError(f"tensors are on {dev} but the current device is cuda:{torch.cuda.current_device()}")
+        if t.get_device() != idx:
+            raise ValueError(f"{name} is on {t.device}, expected {first.device}")
+        if idx < 0:
+            raise ValueError(f"{name} must be a GPU tensor")
+        if not t.is_contiguous():
+            raise ValueError(f"{name} must be contiguous")
+        ptrs.append(t.data_ptr())
+    if idx != torch._C._cuda_getDevice():
+        raise ValueError(f"tensors are on {first.device} but the current device is cuda:{torch.cuda.current_device()}")
+    return ptrs
 
 
 def _layer_shapes(q, v, omega):
@@ -205,12 +216,12 @@ def fwd(q, k, v, r, u, omega, w, eps=EPS, out=None, stats=None, workspace=None,
     chk.append((out, "out", q.shape[:3] + (v.shape[-1],), q.dtype))
     if stats is not None:
         chk.append((stats, "stats", q.shape[:3] + (2,), torch.float32))
-    _expect(chk)
+    ptrs = _expect(chk)
+    if stats is None:
+        ptrs.append(None)
     if workspace is None:
         workspace = alloc_workspace(d, False, q.device)
-    _check(lib().linsimp_fwd(ctypes.byref(d), _ptr(q, "q"), _ptr(k, "k"), _ptr(v, "v"),
-                             _ptr(r, "r"), _ptr(u, "u"), _ptr(omega, "omega"), _ptr(out, "out"),
-                             _ptr(stats, "stats"), _ptr(workspace, "workspace"),
+    _check(lib().linsimp_fwd(ctypes.byref(d), *ptrs, _ptr(workspace, "workspace"),
                              workspace.numel(), _stream()))
     return out, stats
 
@@ -231,10 +242,10 @@ def fwd_static(q, k, v, r, u, omega, w, eps=EPS, out=None, stats=None, want_stat
     chk.append((out, "out", q.shape[:3] + (v.shape[-1],), q.dtype))
     if stats is not None:
         chk.append((stats, "stats", q.shape[:3] + (2,), torch.float32))
-    _expect(chk)
-    _check(lib().linsimp_fwd_static(ctypes.byref(d), _ptr(q, "q"), _ptr(k, "k"), _ptr(v, "v"),
-                                    _ptr(r, "r"), _ptr(u, "u"), _ptr(omega, "omega"), _ptr(out, "out"),
-                                    _ptr(stats, "stats"), _stream()))
+    ptrs = _expect(chk)
+    if stats is None:
+        ptrs.append(None)
+    _check(lib().linsimp_fwd_static(ctypes.byref(d), *ptrs, _stream()))
     return out, stats
 
 
@@ -252,16 +263,12 @@ def bwd(q, k, v, r, u, omega, w, out, stats, dout, eps=EPS, grads=None, workspac
     chk += [(out, "out", ov, q.dtype), (stats, "stats", q.shape[:3] + (2,), torch.float32),
             (dout, "dout", ov, q.dtype)]
     chk += [(g, "d" + nm, x.shape, x.dtype) for g, nm, x in zip(grads, "qkvru", (q, k, v, r, u))]
-    _expect(chk)
+    ptrs = _expect(chk)
     if workspace is None:
         if reuse_states:
             raise ValueError("reuse_states needs the workspace of the matching forward call")
         workspace = alloc_workspace(d, True, q.device)
-    _check(lib().linsimp_bwd_ex(ctypes.byref(d), _ptr(q, "q"), _ptr(k, "k"), _ptr(v, "v"),
-                                _ptr(r, "r"), _ptr(u, "u"), _ptr(omega, "omega"), _ptr(out, "out"),
-                                _ptr(stats, "stats"), _ptr(dout, "dout"), _ptr(dq, "dq"),
-                                _ptr(dk, "dk"), _ptr(dv, "dv"), _ptr(dr, "dr"), _ptr(du, "du"),
-                                BWD_REUSE_STATES if reuse_states else 0,
+    _check(lib().linsimp_bwd_ex(ctypes.byref(d), *ptrs, BWD_REUSE_STATES if reuse_states else 0,
                                 _ptr(workspace, "workspace"), workspace.numel(), _stream()))
     return dq, dk, dv, dr, du
 
@@ -287,9 +294,9 @@ def prefill(k, v, r, u, omega, w, eps=EPS, workspace=None):
     """Decode state after a prefix (k, v, r, u: [S, H, n, *]).  Returns a dict
     with M [S,H,m,Dv], a [S,H,m], rho [S,H] (log2 frame), ring_r, ring_u, pos."""
     S, H, n, D, Dv, m = _layer_shapes(k, v, omega)
-    _expect([(k, "k", (S, H, n, D), k.dtype), (v, "v", (S, H, n, Dv), k.dtype),
-             (r, "r", (S, H, n, D), k.dtype), (u, "u", (S, H, n, Dv), k.dtype),
-             (omega, "omega", (H, m, D), torch.float32)])
+    ptrs = _expect([(k, "k", (S, H, n, D), k.dtype), (v, "v", (S, H, n, Dv), k.dtype),
+                    (r, "r", (S, H, n, D), k.dtype), (u, "u", (S, H, n, Dv), k.dtype),
+                    (omega, "omega", (H, m, D), torch.float32)])
     d = make_dims(S, H, n, D, Dv, m, w, _dtype_code(k), eps)
     dev = k.device
     st = {"M": torch.empty(S, H, m, Dv, dtype=torch.float32, device=dev),
@@ -300,12 +307,8 @@ def prefill(k, v, r, u, omega, w, eps=EPS, workspace=None):
           "pos": torch.empty(S, dtype=torch.int64, device=dev)}
     if workspace is None:
         workspace = alloc_workspace(d, False, dev)
-    _check(lib().linsimp_prefill(ctypes.byref(d), _ptr(k, "k"), _ptr(v, "v"), _ptr(r, "r"),
-                                 _ptr(u, "u"), _ptr(omega, "omega"), _ptr(st["M"], "M"),
-                                 _ptr(st["a"], "a"), _ptr(st["rho"], "rho"),
-                                 _ptr(st["ring_r"], "ring_r"), _ptr(st["ring_u"], "ring_u"),
-                                 _ptr(st["pos"], "pos"), _ptr(workspace, "workspace"),
-                                 workspace.numel(), _stream()))
+    _check(lib().linsimp_prefill(ctypes.byref(d), *ptrs, *[t.data_ptr() for t in st.values()],
+                                 _ptr(workspace, "workspace"), workspace.numel(), _stream()))
     return st
 
 
@@ -316,28 +319,22 @@ def _decode_checks(state, q, k, v, r, u, omega, w, out, tok):
     S, H, D = q.shape[0], q.shape[1], q.shape[-1]
     Dv, m, dt = v.shape[-1], omega.shape[1], q.dtype
     f32 = torch.float32
-    _expect([(q, "q", (S, H, *tok, D), dt), (k, "k", (S, H, *tok, D), dt), (v, "v", (S, H, *tok, Dv), dt),
-             (r, "r", (S, H, *tok, D), dt), (u, "u", (S, H, *tok, Dv), dt),
-             (omega, "omega", (H, m, D), f32), (state["M"], "M", (S, H, m, Dv), f32),
-             (state["a"], "a", (S, H, m), f32), (state["rho"], "rho", (S, H), f32),
-             (state["ring_r"], "ring_r", (S, H, w, D), dt), (state["ring_u"], "ring_u", (S, H, w, Dv), dt),
-             (state["pos"], "pos", (S,), torch.int64), (out, "out", (S, H, *tok, Dv), dt)])
-    return S, H, D, Dv, m
+    sD, sV = (S, H, *tok, D), (S, H, *tok, Dv)
+    ptrs = _expect([(q, "q", sD, dt), (k, "k", sD, dt), (v, "v", sV, dt), (r, "r", sD, dt), (u, "u", sV, dt),
+                    (omega, "omega", (H, m, D), f32), (state["M"], "M", (S, H, m, Dv), f32),
+                    (state["a"], "a", (S, H, m), f32), (state["rho"], "rho", (S, H), f32),
+                    (state["ring_r"], "ring_r", (S, H, w, D), dt), (state["ring_u"], "ring_u", (S, H, w, Dv), dt),
+                    (state["pos"], "pos", (S,), torch.int64), (out, "out", sV, dt)])
+    return S, H, D, Dv, m, ptrs
 
 
 def decode_step(state, q, k, v, r, u, omega, w, eps=EPS, out=None):
     """One decode step for S sequences (q, k, v, r, u: [S, H, *]); updates
     ``state`` in place and returns out [S, H, Dv]."""
     if out is None:
-        out = torch.empty(q.shape[:2] + (v.shape[-1],), dtype=q.dtype, device=q.device)
-    S, H, D, Dv, m = _decode_checks(state, q, k, v, r, u, omega, w, out, ())
-    _check(lib().linsimp_decode_step(S, H, D, Dv, m, w, _dtype_code(q), eps, _ptr(q, "q"),
-                                     _ptr(k, "k"), _ptr(v, "v"), _ptr(r, "r"), _ptr(u, "u"),
-                                     _ptr(omega, "omega"), _ptr(state["M"], "M"),
-                                     _ptr(state["a"], "a"), _ptr(state["rho"], "rho"),
-                                     _ptr(state["ring_r"], "ring_r"),
-                                     _ptr(state["ring_u"], "ring_u"), _ptr(state["pos"], "pos"),
-                                     _ptr(out, "out"), _stream()))
+        out = q.new_empty(q.shape[:2] + (v.shape[-1],))
+    S, H, D, Dv, m, ptrs = _decode_checks(state, q, k, v, r, u, omega, w, out, ())
+    _check(lib().linsimp_decode_step(S, H, D, Dv, m, w, _dtype_code(q), eps, *ptrs, _stream()))
     return out
 
 
@@ -347,14 +344,8 @@ def decode_chunk(state, q, k, v, r, u, omega, w, eps=EPS, out=None):
     if out is None:
         out = torch.empty(q.shape[:3] + (v.shape[-1],), dtype=q.dtype, device=q.device)
     T = q.shape[2]
-    S, H, D, Dv, m = _decode_checks(state, q, k, v, r, u, omega, w, out, (T,))
-    _check(lib().linsimp_decode_chunk(S, H, T, D, Dv, m, w, _dtype_code(q), eps, _ptr(q, "q"),
-                                      _ptr(k, "k"), _ptr(v, "v"), _ptr(r, "r"), _ptr(u, "u"),
-                                      _ptr(omega, "omega"), _ptr(state["M"], "M"),
-                                      _ptr(state["a"], "a"), _ptr(state["rho"], "rho"),
-                                      _ptr(state["ring_r"], "ring_r"),
-                                      _ptr(state["ring_u"], "ring_u"), _ptr(state["pos"], "pos"),
-                                      _ptr(out, "out"), _stream()))
+    S, H, D, Dv, m, ptrs = _decode_checks(state, q, k, v, r, u, omega, w, out, (T,))
+    _check(lib().linsimp_decode_chunk(S, H, T, D, Dv, m, w, _dtype_code(q), eps, *ptrs, _stream()))
     return out
 
 
