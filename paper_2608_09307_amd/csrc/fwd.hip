@@ -767,7 +767,10 @@ __global__ __launch_bounds__(64 * NW) void k_readout(FwdArgs a) {
       for (int sp = 0; sp < F::CSTEPS; ++sp) ppf[sp] = F::cfrag(accP, sp);
       // per 32-wide slice of d: boundary readout + correction, then the anchor
       // combine N += A_c (*) u_c  (lanes <-> d, regs <-> anchor)
-#pragma unroll 1
+      // (unrolled up to two slices; four would spill 47 of the 168 registers that
+      // three waves per SIMD leave)
+      constexpr int kUnroll = DV / 32 <= 2 ? DV / 32 : 1;
+#pragma unroll kUnroll
       for (int dt = 0; dt < DV / 32; ++dt) {
         no_hoist();
         f32x16 accA = zero16();
@@ -784,7 +787,7 @@ __global__ __launch_bounds__(64 * NW) void k_readout(FwdArgs a) {
 #pragma unroll
         for (int sp = 0; sp < F::CSTEPS; ++sp) accA = F::mma(ppf[sp], F::ldc(vrow, 0, sp, h), accA);
         // anchor row index crow(v,h) = 8*(v>>2) + 4h + (v&3) -> window index falls with it
-        float sacc = 0.0f;
+        float sacc = 0.0f, sacc1 = 0.0f;
         if constexpr (sizeof(T) == 2) {
           // u of the register's anchor at this lane's d: transposed reads of rows
           // t + 32 NA - 1 - 32 an - crow, in crow order
@@ -793,14 +796,23 @@ __global__ __launch_bounds__(64 * NW) void k_readout(FwdArgs a) {
           for (int sp = 0; sp < F::CSTEPS; ++sp) {
             const f16x8 uf = __builtin_bit_cast(f16x8, F::tld_crow_map(sUt, DV + C::TPU, sp, dt * 32, rmap));
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sacc = __builtin_fmaf(accA[8 * sp + e], (float)uf[e], sacc);
+            for (int e = 0; e < 8; e += 2) {
+              sacc = __builtin_fmaf(accA[8 * sp + e], (float)uf[e], sacc);
+              sacc1 = __builtin_fmaf(accA[8 * sp + e + 1], (float)uf[e + 1], sacc1);
+            }
           }
+          sacc += sacc1;
         } else {
           const T* urow = sUt + (dt * 32 + col) * UST + (t + 32 * NA - 1 - 32 * an) - 4 * h;
 #pragma unroll
           for (int v = 0; v < 16; ++v) sacc += accA[v] * tof(urow[-(8 * (v >> 2) + (v & 3))]);
         }
-        nacc[dt] += sacc;
+        // nacc[dt] += sacc with the slices rotated through nacc[0], so that the
+        // register is fixed (an index by dt would be a chain of selects)
+        const float x0 = nacc[0] + sacc;
+#pragma unroll
+        for (int i = 1; i < DV / 32; ++i) nacc[i - 1] = nacc[i];
+        nacc[DV / 32 - 1] = x0;
       }
         zacc += zc;
     }
