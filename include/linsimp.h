@@ -192,9 +192,9 @@ int linsimp_decode_step(int64_t S, int32_t H, int32_t D, int32_t Dv, int32_t m, 
 
 /* T consecutive decode steps in one call (Theorem 1 applied T times): token j
  * of sequence s is position pos[s] + j; the result equals T calls of
- * linsimp_decode_step.  The state stays on chip for the whole chunk (M, for
- * m <= 128, in registers; the ring and a in LDS/registers), so it is read and
- * written once per call instead of once per token.
+ * linsimp_decode_step.  The state stays on chip for the whole call (M and a in
+ * registers, the anchors in LDS), so it is read and written once per call
+ * instead of once per token.
  *   q, k, r : [S, H, T, D] dtype;  v, u : [S, H, T, Dv] dtype; omega [H, m, D] f32
  *   M, a, rho, ring_r, ring_u, pos : in/out, layouts as in linsimp_prefill
  *   out : [S, H, T, Dv] dtype

@@ -232,8 +232,8 @@ static int check_dims(const linsimp_dims* d, Shape* s, bool backward, bool bh_on
   return LINSIMP_OK;
 }
 
-// the decode kernels run one 256-thread workgroup per (sequence, head) on a
-// one-dimensional grid, whose thread count must stay below 2^32
+// the decode kernel runs one workgroup per (sequence, head) on a one-dimensional
+// grid, whose thread count must stay below 2^32
 static int check_decode_grid(int64_t S, int32_t H) {
   if (S * (int64_t)H > kMaxDecodeGroups) {
     set_error("decode: S*H = %lld (sequence, head) pairs, at most %lld per call",
