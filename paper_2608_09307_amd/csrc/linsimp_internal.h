@@ -108,8 +108,10 @@ constexpr int64_t kMaxDecodeGroups = ((int64_t)1 << 24) - 1;
 template <typename K>
 inline int64_t kernel_slots(K kernel, int threads) {
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kernel, threads, 0) != hipSuccess) per_cu = 0;
-  (void)hipGetLastError();
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kernel, threads, 0) != hipSuccess) {
+    (void)hipGetLastError();                           // this query's error, not an earlier launch's
+    per_cu = 0;
+  }
   return 256 * (int64_t)(per_cu > 0 ? per_cu : 1);
 }
 
