@@ -227,6 +227,32 @@ LS_DEV void masked_ratios(float (&sj)[16], const float* sRat, int t) {
   }
 }
 
+// The sweeps below factor 2^(R_j - R_i) (j <= i, at most 1) into 2^(R_j - Rref)
+// of the staged rows and 2^(Rref - R_i) of the item's row: a multiply per row
+// where the ratio itself would be an exponential per pair.  That holds only
+// while the frames lie near Rref; 127 powers of two above it the first factor
+// overflows and the second is zero.  Staged rows whose frames reach further
+// than 2^kSpan are therefore walked in groups, each in a reference frame of its
+// own (frames do not fall along a sequence, so a group is a run of rows; 2^64
+// leaves a row's gradient 2^62 of float32's range below it).  The reference
+// moves by whole powers of two, which rescale the staged boundary state exactly.
+// Ordinary frames pay the test only: 2 x 16 heads x 16384 tokens, d = m = 128,
+// du 3.65 -> 3.67 ms and dq/dr 6.53 -> 6.53; d = 128, m = 64, w = 100, 2 x 8 x
+// 3001 dq/dr 0.568 -> 0.579.
+static constexpr float kSpan = 64.0f;
+
+// The group of staged rows from g0 on (rj: their frames, nrow of them).  Rref
+// moves up to within one below the frame of row g0, f is the boundary state's
+// factor for that move.  Returns the first row past the group.
+LS_DEV int next_group(const float* rj, int g0, int nrow, float& Rref, float& f) {
+  const float up = floorf(uniform(rj[g0]) - Rref);
+  f = __builtin_ldexpf(1.0f, -(int)fminf(up, 512.0f));
+  Rref = uniform(Rref + up);
+  int g1 = g0 + 1;
+  while (g1 < nrow && uniform(rj[g1]) - Rref <= kSpan) ++g1;
+  return g1;
+}
+
 // ---------------------------------------------------------------------------
 // k_bwd_du: du_c = sum_i dN_i (*) A_ic,  A_ic = psi_ic^T M^(i)  (regs <-> anchor,
 // lanes <-> d).  A workgroup stages once the boundary state M_b of its own
@@ -301,7 +327,7 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_du(BwdArgs a) {
   // whose boundary state is zero, takes R of its first row); then
   //   A_ic = 2^(Rref - R_i) [psi_c^T M_b + sum_{c0 <= j <= i} 2^(R_j - Rref) (chi_j . psi_c) v_j^T]
   // and the row factor 2^(Rref - R_i) goes into dN_i
-  const float Rref = uniform(has_bnd ? Rexb : a.rj[seq + c0]);
+  float Rref = uniform(has_bnd ? Rexb : a.rj[seq + c0]);
 
   // ---- staging, once per workgroup ----
   {
@@ -454,10 +480,28 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_du(BwdArgs a) {
         for (int v = 0; v < 16; ++v) du[d0 + g][v] += accA[g][v] * ((pair && crow(v, h) > t) ? dNB[d0 + g] : dNA[d0 + g]);
     }
   };
+  // far frames: every row alone, group by group
+  const int nrow = min(ROWS, n - c0);
+  const bool far = uniform(sRj[nrow - 1]) - Rref > kSpan;
+  if (!far) {
 #pragma unroll 1
-  for (int it = wv; it < 32; it += NW) item(it, std::true_type{});
+    for (int it = wv; it < 32; it += NW) item(it, std::true_type{});
 #pragma unroll 1
-  for (int it = 32 + wv; it < 32 * NA; it += NW) item(it, std::false_type{});
+    for (int it = 32 + wv; it < 32 * NA; it += NW) item(it, std::false_type{});
+  } else {
+#pragma unroll 1
+    for (int r0 = 0; r0 < nrow;) {
+      __syncthreads();
+      float f;
+      const int r1 = next_group(sRj, r0, nrow, Rref, f);
+      for (int e = tid; e < DV * (FB + PAD); e += NT) sMt[e] = (T)((float)sMt[e] * f);
+      for (int j = tid; j < nrow; j += NT) sRat[j] = fast_exp2(sRj[j] - Rref);
+      __syncthreads();
+#pragma unroll 1
+      for (int it = r0 + wv; it < r1; it += NW) item(it, std::false_type{});
+      r0 = r1;
+    }
+  }
   reduce_waves<DV / 32>(du, (float*)smem, wv, NW);
   if (wv == 0) {
 #pragma unroll
@@ -549,8 +593,9 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
   for (int Dt = 0; Dt < D / 32; ++Dt) dr[Dt] = zero16();
   const int ch_end = min(nch - 1, (c0 + 30 + w) / 32);
 
+  // (a chunk with far frames is taken once per group of its rows, from row g0 on)
 #pragma unroll 1
-  for (int ch = kt; ch <= ch_end; ++ch) {
+  for (int ch = kt, g0 = 0; ch <= ch_end;) {
     const int s0 = ch * 32;
     const bool has_bnd = ch > 0;
     const float Rexb = a.rex[(size_t)bh * (nch + 1) + ch];
@@ -558,7 +603,7 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
     // whose boundary state is zero, takes R of its first row); with it
     //   dpsi = 2^(Rref - R_i) [M_b dA + dZ a_b + sum_{j <= i} 2^(R_j - Rref) chi_j (v_j . dA + dZ)]
     // and the row factor 2^(Rref - R_i) goes into dN and dZ once per row
-    const float Rref = uniform(has_bnd ? Rexb : a.rj[seq + s0]);
+    float Rref = uniform(has_bnd ? Rexb : a.rj[seq + s0]);
     // The rows of the chunk that see the tile, by what they see of it (rel = the
     // chunk's offset from the tile, w the window): rows rel + t <= 15 only its
     // low 16 anchors, rows rel + t >= w + 15 only its high 16, the rest any of
@@ -641,6 +686,17 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
       }
     }
     __syncthreads();
+    const int nrow = min(32, n - s0);
+    const bool far = uniform(sRj[nrow - 1]) - Rref > kSpan;
+    int g1 = 0;
+    if (far) {                                  // the group's rows, all as full ones
+      float f;
+      g1 = next_group(sRj, g0, nrow, Rref, f);
+      for (int e = tid; e < FB * (DV + PAD); e += NT) sMp[e] = (T)((float)sMp[e] * f);
+      if (sizeof(T) == 4 && tid < FB) sA[tid] *= f;
+      if (tid < nrow) sRat[tid] = fast_exp2(sRj[tid] - Rref);
+      __syncthreads();
+    }
 
     // half: -1 a full row tA; 0 / 1 the low / high half of rows tA and tB (tB < 0: none)
     auto item = [&](const int tA, const int tB, const float (&gA)[NG], const float (&gB)[NG], auto half_c) {
@@ -847,25 +903,33 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
     // at most eight pairs of either kind: one per wave.  Upstream-gradient rows
     // are fetched one row ahead, the first full row's before the pairs; the
     // waves left idle by the pairs take the first full rows
-    const int tf0 = tlo + ((wv - nlo - nhi) & (NW - 1));
+    int tf0 = tlo + ((wv - nlo - nhi) & (NW - 1)), tf1 = thi;
+    if (far) {
+      tf0 = g0 + wv;
+      tf1 = min(g1, tend);
+    }
     float gpre[NG];
     load_g(gpre, tf0);
-    if (wv < nlo) item(tl, tl + 1 < tlo ? tl + 1 : -1, gA, gB, std::integral_constant<int, 0>{});
-    const int wh = (wv - nlo) & (NW - 1), th = thi + 2 * wh;
-    if (wh < nhi) {
-      if (nlo > 0) {                              // (narrow windows: the prefetched pair was a low one)
-        load_g(gA, th);
-        load_g(gB, th + 1);
+    if (!far) {
+      if (wv < nlo) item(tl, tl + 1 < tlo ? tl + 1 : -1, gA, gB, std::integral_constant<int, 0>{});
+      const int wh = (wv - nlo) & (NW - 1), th = thi + 2 * wh;
+      if (wh < nhi) {
+        if (nlo > 0) {                            // (narrow windows: the prefetched pair was a low one)
+          load_g(gA, th);
+          load_g(gB, th + 1);
+        }
+        item(th, th + 1 < tend ? th + 1 : -1, gA, gB, std::integral_constant<int, 1>{});
       }
-      item(th, th + 1 < tend ? th + 1 : -1, gA, gB, std::integral_constant<int, 1>{});
     }
 #pragma unroll 1
-    for (int t = tf0; t < thi; t += NW) {
+    for (int t = tf0; t < tf1; t += NW) {
 #pragma unroll
       for (int e = 0; e < NG; ++e) gA[e] = gpre[e];
-      if (t + NW < thi) load_g(gpre, t + NW);
+      if (t + NW < tf1) load_g(gpre, t + NW);
       item(t, -1, gA, gA, std::integral_constant<int, -1>{});
     }
+    g0 = far && g1 < tend ? g1 : 0;
+    if (g0 == 0) ++ch;
   }
   reduce_waves<D / 32>(dr, (float*)smem, wv, NW);
   if (wv == 0) {

@@ -97,3 +97,38 @@ def oracle_backward(x, w, pairs, eps=O.EPS, scales=None):
         if scales is not None:
             scales[(b, h)] = ts["dk"]
     return out
+
+
+def backward_in_frames(x, b, h, w, eps=O.EPS):
+    """The definition's gradients (dq, dk, dv, dr, du) of one (batch, head) by
+    float64 autograd, every row's features taken relative to its own largest
+    query feature and to the largest key feature so far (constants that cancel
+    in the ratio, eps added after them as the library does).  For keys whose
+    features span more than float64 keeps beside each other, where a state
+    that later tokens are subtracted from again holds only their rounding.
+    Also returns dk's absolute term scale per key, as oracle.linsimp.backward's
+    ``term_scale``."""
+    q, k, v, r, u, om, dO = (t.detach().cpu().double() for t in
+                             (*(x[c][b, h] for c in "qkvru"), x["omega"][h], x["dO"][b, h]))
+    leaf = [t.clone().requires_grad_() for t in (q, k, v, r, u)]
+    q, k, v, r, u = leaf
+    n, m = k.shape[0], om.shape[0]
+    lam = k @ om.T - 0.5 * k.square().sum(-1, keepdim=True)
+    top = lam.detach().amax(-1).cummax(0).values
+    loss, terms = 0.0, torch.zeros(n, m, dtype=torch.float64)
+    for i in range(n):
+        c = slice(max(0, i - w + 1), i + 1)
+        z = q[i] * r[c]
+        ell = z @ om.T - 0.5 * z.square().sum(-1, keepdim=True)
+        psi = torch.exp(ell - ell.detach().max())
+        chi = torch.exp(lam[:i + 1] - top[i]) / m ** 0.5
+        P = psi @ chi.T                                       # [anchors, tokens]
+        Z = P.sum() + eps
+        o = ((P @ v[:i + 1]) * u[c] / Z).sum(0)
+        loss = loss + o @ dO[i]
+        with torch.no_grad():
+            t = ((dO[i] / Z).abs() * u[c].abs()) @ v[:i + 1].abs().T + (o @ dO[i] / Z).abs()
+            terms[:i + 1] += (t.T @ psi) * chi
+    with torch.no_grad():
+        scale = (terms @ om.abs() + terms.sum(-1, keepdim=True) * k.abs()).norm(dim=-1)
+    return [g.numpy() for g in torch.autograd.grad(loss, leaf)], scale.numpy()
