@@ -40,7 +40,9 @@ struct DecArgs {
 // The anchors r, u of the last 32 NA - 1 tokens and of the block's tokens sit in
 // LDS, one row per token in a ring of E = 32 NA + TB rows: token i of the call
 // (i < 0: before it) has row (i + 32 NA) mod E, and its anchor at offset dl the
-// row of token i - dl.  Per block: lambda by float32 dot products (their maxima
+// row of token i - dl; offsets past the window read the one row that is free
+// in a block, kept zero (a -inf bias alone would let an inf or NaN of a token
+// outside the window through).  Per block: lambda by float32 dot products (their maxima
 // give every token's frame R) and the table of |z|^2.  Per token and wave: the
 // state update, the logits L[c, p] = sum_d r_c[d] (q[d] Omega[p, d]) with
 // q (*) Omega rounded once, psi = 2^(L - |z|^2 log2(e)/2 - L_w), W = Psi^T U on
@@ -153,6 +155,9 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
         put((ti == 3 ? sR + row * C::RST : sU + row * C::UST) + c * VE, xt[it]);
       }
     }
+    // the row no token of the block's windows has
+    for (int e = tid; e < D; e += NT) sR[row_of(j0 - AW) * C::RST + e] = (T)0.0f;
+    for (int e = tid; e < DV; e += NT) sU[row_of(j0 - AW) * C::UST + e] = (T)0.0f;
   };
   // The loads of the prologue in the order they are waited for: the first
   // block's tokens, the ring and the bank, staged, then the state, which arrives
@@ -187,9 +192,6 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
       const V zero = {};
       put(c < PR ? sR + row_of(-back) * C::RST + c * VE : sU + row_of(-back) * C::UST + (c - PR) * VE, ok ? x[it] : zero);
     }
-    // the one row no token of the first block's windows has yet
-    for (int e = tid; e < D; e += NT) sR[row_of(-AW) * C::RST + e] = (T)0.0f;
-    for (int e = tid; e < DV; e += NT) sU[row_of(-AW) * C::UST + e] = (T)0.0f;
     place(0);
   }
   // ---- this wave's rows of M and entries of a ----
@@ -274,11 +276,15 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
       }
       // ---- logits (registers <-> anchor offset, lanes <-> p) ----
       const int ib = row_of(j0 + j);
-      auto ring_row = [&](int dl) { const int e = ib - dl; return e < 0 ? e + E : e; };   // dl <= AW - 1 < E
+      // row of the anchor at offset dl <= AW - 1 < E (one token: the rows past the window are zero already)
+      auto ring_row = [&](int dl, bool last) {
+        const int e = ib - dl;
+        return TB > 1 && last && dl >= w ? row_of(j0 - AW) : e < 0 ? e + E : e;
+      };
       const float* qr = sq + j * D;
       const T* arow[NA];
 #pragma unroll
-      for (int an = 0; an < NA; ++an) arow[an] = sR + ring_row(32 * an + col) * C::RST;
+      for (int an = 0; an < NA; ++an) arow[an] = sR + ring_row(32 * an + col, an == NA - 1) * C::RST;
       f32x16 acc[NA];
 #pragma unroll
       for (int an = 0; an < NA; ++an) acc[an] = zero16();
@@ -333,7 +339,7 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
         f32x16 accW = zero16();
 #pragma unroll
         for (int an = 0; an < NA; ++an) {
-          auto rmap = [&](int ar) { return ring_row(32 * an + ar); };
+          auto rmap = [&](int ar) { return ring_row(32 * an + ar, an == NA - 1); };
 #pragma unroll
           for (int sp = 0; sp < F::CSTEPS; ++sp)
             accW = F::mma(pf[an][sp], F::tld_crow_map(sU, C::UST, sp, dt * 32, rmap), accW);

@@ -292,3 +292,47 @@ def test_prefill_state(D, m, n, w, S, H, dt):
 ])
 def test_decode_chunk_block_edges(dtype, D, m, w, P, T):
     test_decode_chunk_matches_steps_and_forward(dtype, D, m, w, P, T)
+
+
+@pytest.mark.parametrize("D,m,w,P,T,dt", [
+    (128, 128, 33, 50, 60, "bf16"),     # one offset of the second anchor tile inside the window
+    (64, 64, 20, 0, 45, "bf16"),
+    (128, 64, 100, 130, 40, "bf16"),    # the bad token is in the ring before the call
+    (64, 32, 63, 70, 75, "f32"),
+    (64, 128, 64, 70, 75, "bf16"),      # a whole number of tiles
+])
+def test_decode_chunk_non_finite_anchor_leaves_with_the_window(D, m, w, P, T, dt):
+    """An anchor with inf or NaN in r or u: the tokens whose windows hold it are
+    non-finite, every other token of the chunked call has the single steps' value."""
+    bad = P + 3 if P < 90 else P - w + 5
+    wl = Workload("badanchor", 2, 2, P + T, D, D, m, w, dt, "fwd", seed=24)
+    print(f"[decode_chunk] {wl} T={T}", flush=True)
+    x = make_inputs(wl, device=DEV, with_grad=False)
+    x["r"][0, 0, bad, 1] = float("inf")
+    x["r"][0, 1, bad, 5] = float("nan")
+    x["u"][1, 0, bad, 2] = float("-inf")
+    x["u"][1, 1, bad, 7] = float("nan")
+
+    def fresh():
+        if P > 0:
+            return L.prefill(*(x[nm][:, :, :P].contiguous() for nm in ("k", "v", "r", "u")), x["omega"], w)
+        z = torch.zeros
+        return {"M": z(2, 2, m, D, device=DEV), "a": z(2, 2, m, device=DEV),
+                "rho": torch.full((2, 2), float("-inf"), device=DEV),
+                "ring_r": z(2, 2, w, D, dtype=x["k"].dtype, device=DEV),
+                "ring_u": z(2, 2, w, D, dtype=x["k"].dtype, device=DEV),
+                "pos": z(2, dtype=torch.int64, device=DEV)}
+
+    st_c, st_s = fresh(), fresh()
+    tok = {nm: x[nm][:, :, P:].contiguous() for nm in "qkvru"}
+    got = f64(L.decode_chunk(st_c, *(tok[nm] for nm in "qkvru"), x["omega"], w))
+    steps = [L.decode_step(st_s, *(tok[nm][:, :, t].contiguous() for nm in "qkvru"), x["omega"], w).clone()
+             for t in range(T)]
+    exp = f64(torch.stack(steps, dim=2))
+    t = np.arange(P, P + T)
+    clean = (t < bad) | (t - bad >= w)
+    assert clean.any() and not clean.all()
+    assert np.isfinite(exp[:, :, clean]).all()
+    assert np.isfinite(got[:, :, clean]).all()
+    assert rel_l2(got[:, :, clean], exp[:, :, clean]) < 1e-6
+    assert not np.isfinite(got[:, :, ~clean]).all(-1).any()
