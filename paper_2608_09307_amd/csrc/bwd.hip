@@ -731,7 +731,7 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_dqdr(BwdArgs a) {
         for (int e = 0; e < NG; ++e)
           if (e * 64 + l < DV) {
             sDN[e * 64 + l] = gA[e] * invrA;
-            sDN[DV + e * 64 + l] = gB[e] * invrB;
+            sDN[DV + e * 64 + l] = tB < 0 ? 0.0f : gB[e] * invrB;   // (no second row: gB is a row that may not see the tile)
           }
       } else {
 #pragma unroll
