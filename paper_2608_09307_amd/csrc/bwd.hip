@@ -401,7 +401,8 @@ __global__ __launch_bounds__(64 * 8) void k_bwd_du(BwdArgs a) {
     const bool okB = pair && iB < n && 32 * NA + t - 31 < w;
     if (!okA && !okB) return;
     // row scalars of the (at most two) rows
-    const int iAc = min(iA, n - 1), iBc = min(iB, n - 1);
+    // (a row B that does not see the tile: A's values, factor zero)
+    const int iAc = min(iA, n - 1), iBc = okB ? iB : iAc;
     const float LA = uniform(a.stats[(seq + iAc) * 2]), LB = uniform(a.stats[(seq + iBc) * 2]);
     const float invA = uniform(a.rowstat[(seq + iAc) * 2]), invB = uniform(a.rowstat[(seq + iBc) * 2]);
     const float RA = uniform(okA ? sRj[rcA * 32 + t] : -kNegInf), RB = uniform(okB ? sRj[32 * NA + t] : -kNegInf);

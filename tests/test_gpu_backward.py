@@ -223,9 +223,9 @@ def test_reuse_flag_refuses_a_workspace_with_other_states():
 
 @pytest.mark.parametrize("D,m,dt", [(64, 64, "bf16"), (128, 128, "bf16"), (32, 32, "f32")])
 def test_backward_non_finite_gradient_stays_in_its_tiles(D, m, dt):
-    """Row 65 at w = 34 sees anchors 32 .. 65: an inf in its dO leaves dr of the
-    first tile's anchors as it was (row 64, the tile's last, is an unpaired
-    half-tile row there)."""
+    """Row 65 at w = 34 sees anchors 32 .. 65: an inf in its dO leaves dr and du
+    of the first tile's anchors as they were (row 64, the tile's last, is an
+    unpaired half-tile row there; row 1's pair in the du sweep is row 65)."""
     wl = Workload("inf_dO", 1, 2, 139, D, D, m, 34, dt, "fwdbwd", seed=50)
     x = make_inputs(wl, device=DEV, with_grad=True)
     args = (x["q"], x["k"], x["v"], x["r"], x["u"], x["omega"], wl.w)
@@ -233,6 +233,6 @@ def test_backward_non_finite_gradient_stays_in_its_tiles(D, m, dt):
     clean = L.bwd(*args, out, stats, x["dO"])
     x["dO"][:, :, 65, 3] = float("inf")
     got = L.bwd(*args, out, stats, x["dO"])
-    i = NAMES.index("dr")
-    assert not torch.isfinite(got[i][:, :, 32:66].float()).all()
-    assert torch.equal(got[i][:, :, :32], clean[i][:, :, :32])
+    for i in (NAMES.index("dr"), NAMES.index("du")):
+        assert not torch.isfinite(got[i][:, :, 32:66].float()).all()
+        assert torch.equal(got[i][:, :, :32], clean[i][:, :, :32])
