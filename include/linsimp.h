@@ -182,8 +182,8 @@ int linsimp_prefill(const linsimp_dims* dims, const void* k, const void* v, cons
  *   M, a, rho, ring_r, ring_u, pos : in/out, layouts as in linsimp_prefill
  *   out : [S, H, Dv] dtype
  * Uses no workspace.  Same shape support as the forward; 1 <= S and
- * S*H <= 2^24 - 1 (one workgroup per (sequence, head); more returns
- * LINSIMP_E_UNSUPPORTED).  pos advances only when the step was enqueued. */
+ * S*H <= 2^24 - 1, at m = 256 2^23 - 1 (one workgroup per (sequence, head);
+ * more returns LINSIMP_E_UNSUPPORTED).  pos advances only when the step was enqueued. */
 int linsimp_decode_step(int64_t S, int32_t H, int32_t D, int32_t Dv, int32_t m, int32_t w,
                         int32_t dtype, float eps, const void* q, const void* k, const void* v,
                         const void* r, const void* u, const float* omega, float* M, float* a,

@@ -234,10 +234,11 @@ static int check_dims(const linsimp_dims* d, Shape* s, bool backward, bool bh_on
 
 // the decode kernel runs one workgroup per (sequence, head) on a one-dimensional
 // grid, whose thread count must stay below 2^32
-static int check_decode_grid(int64_t S, int32_t H) {
-  if (S * (int64_t)H > kMaxDecodeGroups) {
-    set_error("decode: S*H = %lld (sequence, head) pairs, at most %lld per call",
-              (long long)(S * (int64_t)H), (long long)kMaxDecodeGroups);
+static int check_decode_grid(int64_t S, int32_t H, int32_t m) {
+  const int64_t most = max_decode_groups(m);
+  if (S * (int64_t)H > most) {
+    set_error("decode: S*H = %lld (sequence, head) pairs, at most %lld per call at m = %d",
+              (long long)(S * (int64_t)H), (long long)most, m);
     return LINSIMP_E_UNSUPPORTED;
   }
   return LINSIMP_OK;
@@ -359,7 +360,7 @@ int linsimp_decode_step(int64_t S, int32_t H, int32_t D, int32_t Dv, int32_t m, 
   Shape s;
   int rc = check_dims(&d, &s, false, false);
   if (rc) return rc;
-  if ((rc = check_decode_grid(S, H))) return rc;
+  if ((rc = check_decode_grid(S, H, m))) return rc;
   const void* ps[] = {q, k, v, r, u, omega, M, a, rho, ring_r, ring_u, pos, out};
   if ((rc = check_ptrs("q,k,v,r,u,omega,M,a,rho,ring_r,ring_u,pos,out", ps, 13))) return rc;
   return launch_decode(S, H, 1, D, Dv, m, w, dtype, eps, q, k, v, r, u, omega, M, a, rho, ring_r,
@@ -380,7 +381,7 @@ int linsimp_decode_chunk(int64_t S, int32_t H, int32_t T, int32_t D, int32_t Dv,
   Shape s;
   int rc = check_dims(&d, &s, false, false);
   if (rc) return rc;
-  if ((rc = check_decode_grid(S, H))) return rc;
+  if ((rc = check_decode_grid(S, H, m))) return rc;
   const void* ps[] = {q, k, v, r, u, omega, M, a, rho, ring_r, ring_u, pos, out};
   if ((rc = check_ptrs("q,k,v,r,u,omega,M,a,rho,ring_r,ring_u,pos,out", ps, 13))) return rc;
   return launch_decode(S, H, T, D, Dv, m, w, dtype, eps, q, k, v, r, u, omega, M, a, rho, ring_r,

@@ -419,7 +419,8 @@ __global__ __launch_bounds__(256) void k_decode_advance(int64_t* pos, int64_t S,
 
 template <typename T, int D, int DV, int M, int NA>
 static int run_decode(int64_t S, DecArgs a, int ntok, hipStream_t st) {
-  // the caller bounds S*H by kMaxDecodeGroups (one workgroup each)
+  // the caller bounds S*H by max_decode_groups (one workgroup each)
+  static_assert(max_decode_groups(M) * DCfg<T, D, DV, M, NA, 1>::NT < ((int64_t)1 << 32), "decode grid");
   (void)hipGetLastError();                             // an earlier call's error is not this one's
   const unsigned groups = (unsigned)(S * a.H);
   if (ntok == 1) {

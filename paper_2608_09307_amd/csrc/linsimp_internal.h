@@ -99,10 +99,10 @@ int launch_head_reduce(const Shape& s, const float* part, float* out, hipStream_
 int launch_feature_bank(int H, int m, int D, const float* gauss, const float* radii, float* omega,
                         int sign_correct, hipStream_t st);
 
-// (sequence, head) pairs of one decode call: one workgroup of 2 m threads each
-// on a one-dimensional grid of fewer than 2^32 threads (at m = 256, 512 threads,
-// the state of 2^23 pairs would be 1.1 TB)
-constexpr int64_t kMaxDecodeGroups = ((int64_t)1 << 24) - 1;
+// (sequence, head) pairs of one decode call: one workgroup each, of at most 256
+// threads up to m = 128 and 512 at m = 256, on a one-dimensional grid of fewer
+// than 2^32 threads
+constexpr int64_t max_decode_groups(int m) { return ((int64_t)1 << (m > 128 ? 23 : 24)) - 1; }
 
 // Workgroups of a kernel that run at once on the chip (256 CUs)
 template <typename K>

@@ -125,14 +125,19 @@ def test_reuse_flag_without_a_matching_forward_is_refused():
 
 
 def test_decode_grid_bound_is_an_error():
-    """One workgroup per (sequence, head): S*H above 2^24 - 1 is refused
-    (LINSIMP_E_UNSUPPORTED) before any launch."""
+    """One workgroup per (sequence, head): S*H above 2^24 - 1, at m = 256 (twice
+    the threads) above 2^23 - 1, is refused (LINSIMP_E_UNSUPPORTED) before any
+    launch."""
     lib = L.lib()
     vp = ctypes.c_void_p
     ptrs = [vp(4096 * (i + 1)) for i in range(13)]
     rc = lib.linsimp_decode_step(1 << 20, 16, 32, 32, 32, 8, L.BF16, 1e-30, *ptrs, vp(0))
     assert rc == -2 and b"at most" in lib.linsimp_last_error()
     rc = lib.linsimp_decode_chunk(1 << 20, 16, 2, 32, 32, 32, 8, L.BF16, 1e-30, *ptrs, vp(0))
+    assert rc == -2
+    rc = lib.linsimp_decode_step(1 << 19, 16, 128, 128, 256, 8, L.BF16, 1e-30, *ptrs, vp(0))
+    assert rc == -2 and b"at most" in lib.linsimp_last_error()
+    rc = lib.linsimp_decode_chunk(1 << 19, 16, 2, 128, 128, 256, 8, L.BF16, 1e-30, *ptrs, vp(0))
     assert rc == -2
 
 
