@@ -10,6 +10,8 @@
 // The readout uses the contraction order W = Psi^T U (matrix cores, sum over
 // anchors), then N_d = sum_p M[p,d] W[p,d] fused with the state update, so
 // every float32 state element is read once and written once.
+#include <type_traits>
+
 #include "common.h"
 #include "linsimp_internal.h"
 #include "prof.h"
@@ -31,20 +33,20 @@ struct DecArgs {
 // position pos[s] + j), in blocks of TB: TB = 1 for the single step, whose
 // token loop unrolls away, 8 otherwise; a token's arithmetic is the same in
 // both, so T tokens in one call give the bits of T single steps.  One workgroup
-// per (sequence, head), one wave per 32 features; each wave keeps its rows of M
-// and of the bank (float32) in registers, its entries of a, and a row shift L_w
-// of its own (over its features only), so the waves walk the tokens of a block
-// without meeting; the parts of N and Z are brought together, in order, once
-// per block.
+// per (sequence, head), one wave per 32 features (with one feature tile, per
+// group of its anchors); each wave keeps its rows of M and of the bank (float32)
+// in registers, its entries of a, and a row shift L_w of its own (over its
+// features only), so the waves walk the tokens of a block without meeting; the
+// parts of N and Z are brought together, in order, once per block.
 //
 // The anchors r, u of the last 32 NA - 1 tokens and of the block's tokens sit in
 // LDS, one row per token in a ring of E = 32 NA + TB rows: token i of the call
 // (i < 0: before it) has row (i + 32 NA) mod E, and its anchor at offset dl the
 // row of token i - dl; offsets past the window read the one row that is free
 // in a block, kept zero (a -inf bias alone would let an inf or NaN of a token
-// outside the window through).  Per block: lambda by float32 dot products (their maxima
-// give every token's frame R) and the table of |z|^2.  Per token and wave: the
-// state update, the logits L[c, p] = sum_d r_c[d] (q[d] Omega[p, d]) with
+// outside the window through).  Per block: lambda by float32 dot products (their
+// maxima give every token's frame R) and the table of |z|^2.  Per token and wave:
+// the state update, the logits L[c, p] = sum_d r_c[d] (q[d] Omega[p, d]) with
 // q (*) Omega rounded once, psi = 2^(L - |z|^2 log2(e)/2 - L_w), W = Psi^T U on
 // the matrix cores, N += M (*) W.
 //
@@ -58,7 +60,21 @@ struct DecArgs {
 // ---------------------------------------------------------------------------
 template <typename T, int D, int DV, int M, int NA, int TB>
 struct DCfg {
-  static constexpr int NW = M / 32, NT = 64 * NW;
+  static constexpr int FT = M / 32;                              // feature tiles
+  // Anchor groups.  N and Z are linear in the anchors, so in a workgroup of one
+  // feature tile every group of anchor tiles gets a wave of its own, with its own
+  // copy of the state and its own row shift; their parts are added with the other
+  // waves'.  One wave alone ran a wide window's tiles in series and, in float32,
+  // kept their logits in accumulation registers at one wave per SIMD: one step of
+  // 16 heads, w = 128, float32 d = 64 22.0 -> 14.2 us, bf16 d = 32 9.2 -> 7.7;
+  // 32 x 16, 16 tokens, float32 d = 64 480 -> 166.  (The copies of the state cost
+  // more than the waves give only where a batch fills the chip: 64 x 16, 64
+  // tokens, w = 96, bf16 164 -> 175, float32 d = 32 374 -> 410.)
+  static constexpr bool F32 = sizeof(T) == 4;
+  static constexpr int AH = FT > 1 ? 1 : F32 ? (D * NA >= 96 ? NA : 1) : NA == 4 ? 2 : NA == 3 ? 3 : 1;
+  static constexpr int WPE = AH > 1 && F32 && D == 32 ? 3 : 2;   // waves per SIMD
+  static constexpr int NAW = NA / AH;                            // anchor tiles per wave
+  static constexpr int NW = FT * AH, NT = 64 * NW;
   static constexpr int AW = 32 * NA, E = AW + TB;
   static constexpr int RST = D + MF<T>::PAD, UST = DV + tr_pad<T, DV>();
   static constexpr int ES = sizeof(T);
@@ -77,10 +93,11 @@ struct DCfg {
 };
 
 template <typename T, int D, int DV, int M, int NA, int TB>
-__global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int ntok) {
+__global__ __launch_bounds__((DCfg<T, D, DV, M, NA, TB>::NT), (DCfg<T, D, DV, M, NA, TB>::WPE)) void k_decode(DecArgs A, int ntok) {
   using F = MF<T>;
   using C = DCfg<T, D, DV, M, NA, TB>;
   constexpr int NW = C::NW, NT = C::NT, AW = C::AW, E = C::E, NS = D / F::KS;
+  constexpr int FT = C::FT, AH = C::AH, NAW = C::NAW;
   const int NTOK = TB == 1 ? 1 : ntok;
   static_assert(C::BYTES <= 160 * 1024, "decode LDS budget");
   __shared__ __align__(16) char smem[C::BYTES];
@@ -94,6 +111,8 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
   float* sZ = (float*)(smem + C::oZ);
 
   const int tid = threadIdx.x, l = tid & 63, col = l & 31, h = l >> 5, wv = uniform(tid >> 6);
+  const int wp = AH == 1 ? wv : wv % FT;                       // this wave's feature tile
+  const int a0 = AH == 1 ? 0 : 32 * NAW * (wv / FT);           // first anchor offset of its group
   float* schi = (float*)(smem + C::oChi) + wv * 32;
   float* slam = (float*)(smem + C::oLam) + wv * TB * 32;
   const int sh = blockIdx.x, H = A.H, w = A.w;
@@ -113,11 +132,19 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
   constexpr int VE = 16 / (int)sizeof(T);
   typedef T V __attribute__((ext_vector_type(VE)));
   // a block's token rows: q, k, v as float32, r and u into the ring
-  static_assert(D == DV && (NT & (NT - 1)) == 0, "rows of one width, thread mask");
+  static_assert(D == DV, "rows of one width");
   constexpr int PD = D / VE, PT = 5 * PD, NP = TB * PT, PIT = (NP + NT - 1) / NT;
   // (thread numbers made opaque where a block or a token starts: the addresses
   // are formed there instead of being held in registers across the loops)
-  auto opaque = [](int x, int mask) { asm volatile("" : "+v"(x)); return x & mask; };
+  auto opaque = [](int x, auto count) {
+    constexpr int N = decltype(count)::value;
+    asm volatile("" : "+v"(x));
+    if constexpr ((N & (N - 1)) == 0) return x & (N - 1);      // (its range, which the compiler no longer knows)
+    __builtin_assume(x >= 0 && x < N);
+    return x;
+  };
+  constexpr std::integral_constant<int, NT> threads{};
+  constexpr std::integral_constant<int, 64> lanes{};
   // one piece into an LDS row (float32 rows are padded by one element: not 16-byte aligned)
   auto put = [](T* dst, const V& x) {
     if constexpr (sizeof(T) == 2) *(V*)dst = x;
@@ -128,7 +155,7 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
   };
   V xt[PIT];
   auto fetch = [&](int j0) {
-    const int tid = opaque(threadIdx.x, NT - 1);
+    const int tid = opaque(threadIdx.x, threads);
 #pragma unroll
     for (int it = 0; it < PIT; ++it) {
       const int idx = min(tid + NT * it, NP - 1), j = min(j0 + idx / PT, NTOK - 1), ti = idx % PT / PD, c = idx % PD;
@@ -141,7 +168,7 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
     }
   };
   auto place = [&](int j0) {
-    const int tid = opaque(threadIdx.x, NT - 1);
+    const int tid = opaque(threadIdx.x, threads);
 #pragma unroll
     for (int it = 0; it < PIT; ++it) {
       const int idx = tid + NT * it, jj = idx / PT, ti = idx % PT / PD, c = idx % PD;
@@ -166,7 +193,7 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
   // ---- this wave's bank rows (Omega log2 e, lanes <-> p, the operand's pieces of D) ----
   float om[NS][F::KPL];
   {
-    const float* orow = A.omega + ((size_t)hh * M + wv * 32 + col) * D + h * F::KPL;
+    const float* orow = A.omega + ((size_t)hh * M + wp * 32 + col) * D + h * F::KPL;
 #pragma unroll
     for (int ks = 0; ks < NS; ++ks)
 #pragma unroll
@@ -199,8 +226,8 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
 #pragma unroll
   for (int dt = 0; dt < DV / 32; ++dt)
 #pragma unroll
-    for (int vv = 0; vv < 16; ++vv) Mreg[dt][vv] = Ms[(size_t)(wv * 32 + crow(vv, h)) * DV + dt * 32 + col];
-  float areg = as[wv * 32 + col];
+    for (int vv = 0; vv < 16; ++vv) Mreg[dt][vv] = Ms[(size_t)(wp * 32 + crow(vv, h)) * DV + dt * 32 + col];
+  float areg = as[wp * 32 + col];
   float R = A.rho[sh];
 
 #pragma unroll 1
@@ -211,7 +238,7 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
     // anchor, each every TPA-th 16-byte piece of the row, their sums added in order ----
     {
       constexpr int TPA = NT >= AW ? (NT / AW >= 4 ? 4 : NT / AW >= 2 ? 2 : 1) : 1, APP = NT / TPA;
-      const int tid = opaque(threadIdx.x, NT - 1), part = tid % TPA;
+      const int tid = opaque(threadIdx.x, threads), part = tid % TPA;
 #pragma unroll 1
       for (int idx = tid / TPA; idx < nb * AW; idx += APP) {
         const int j = idx / AW, dl = idx % AW, i = j0 + j;
@@ -236,7 +263,7 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
     // ---- key log2-features of the block's tokens (float32) and their maxima ----
 #pragma unroll 1
     for (int j = 0; j < nb; ++j) {
-      const int l = opaque(lane_id(), 63), col = l & 31, h = l >> 5;
+      const int l = opaque(lane_id(), lanes), col = l & 31, h = l >> 5;
       const float* kr = sk + j * D;
       float nk = 0.0f, lam = 0.0f;
 #pragma unroll
@@ -244,7 +271,7 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
       nk = wave_sum(nk);
 #pragma unroll
       for (int ks = 0; ks < NS; ++ks) {
-        if (ks % 4 == 0) no_hoist();                           // a few reads in flight, not all of the row
+        if (ks % (sizeof(T) == 4 ? 16 : 4) == 0) no_hoist();                         // a few reads in flight, not all of the row
 #pragma unroll
         for (int e = 0; e < F::KPL; ++e) lam = __builtin_fmaf(om[ks][e], kr[ks * F::KS + h * F::KPL + e], lam);
       }
@@ -257,7 +284,7 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
 
 #pragma unroll 1
     for (int j = 0; j < nb; ++j) {
-      const int l = opaque(lane_id(), 63), col = l & 31, h = l >> 5;
+      const int l = opaque(lane_id(), lanes), col = l & 31, h = l >> 5;
       // ---- the frame, chi and a ----
       float Rn = R;
 #pragma unroll
@@ -282,15 +309,15 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
         return TB > 1 && last && dl >= w ? row_of(j0 - AW) : e < 0 ? e + E : e;
       };
       const float* qr = sq + j * D;
-      const T* arow[NA];
+      const T* arow[NAW];
 #pragma unroll
-      for (int an = 0; an < NA; ++an) arow[an] = sR + ring_row(32 * an + col, an == NA - 1) * C::RST;
-      f32x16 acc[NA];
+      for (int an = 0; an < NAW; ++an) arow[an] = sR + ring_row(a0 + 32 * an + col, AH > 1 || an == NA - 1) * C::RST;
+      f32x16 acc[NAW];
 #pragma unroll
-      for (int an = 0; an < NA; ++an) acc[an] = zero16();
+      for (int an = 0; an < NAW; ++an) acc[an] = zero16();
 #pragma unroll
       for (int ks = 0; ks < NS; ++ks) {
-        if (ks % 2 == 0) no_hoist();
+        if (ks % (sizeof(T) == 4 ? 4 : 2) == 0) no_hoist();
         const int k0 = ks * F::KS + h * F::KPL;
         typename F::frag b;
         if constexpr (sizeof(T) == 2) {
@@ -301,13 +328,13 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
           b = om[ks][0] * qr[k0];
         }
 #pragma unroll
-        for (int an = 0; an < NA; ++an) acc[an] = F::mma(F::ld(arow[an], k0), b, acc[an]);
+        for (int an = 0; an < NAW; ++an) acc[an] = F::mma(F::ld(arow[an], k0), b, acc[an]);
       }
       float tm = kNegInf;
 #pragma unroll
-      for (int an = 0; an < NA; ++an) {
+      for (int an = 0; an < NAW; ++an) {
         float bias[16];
-        crow_vals(sNz + j * AW + 32 * an, bias);
+        crow_vals(sNz + j * AW + a0 + 32 * an, bias);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           acc[an][v] += bias[v];
@@ -315,13 +342,14 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
         }
       }
       const float L = wave_max(tm);
+      const float Ls = AH > 1 && L == kNegInf ? 0.0f : L;      // (a group without an anchor yet: psi = 0)
       float ps = 0.0f;
-      typename F::frag pf[NA][F::CSTEPS];
+      typename F::frag pf[NAW][F::CSTEPS];
 #pragma unroll
-      for (int an = 0; an < NA; ++an) {
+      for (int an = 0; an < NAW; ++an) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          acc[an][v] = fast_exp2(acc[an][v] - L);
+          acc[an][v] = fast_exp2(acc[an][v] - Ls);
           ps += acc[an][v];
         }
 #pragma unroll
@@ -338,8 +366,8 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
         no_hoist();
         f32x16 accW = zero16();
 #pragma unroll
-        for (int an = 0; an < NA; ++an) {
-          auto rmap = [&](int ar) { return ring_row(32 * an + ar, an == NA - 1); };
+        for (int an = 0; an < NAW; ++an) {
+          auto rmap = [&](int ar) { return ring_row(a0 + 32 * an + ar, AH > 1 || an == NA - 1); };
 #pragma unroll
           for (int sp = 0; sp < F::CSTEPS; ++sp)
             accW = F::mma(pf[an][sp], F::tld_crow_map(sU, C::UST, sp, dt * 32, rmap), accW);
@@ -383,11 +411,13 @@ __global__ __launch_bounds__((64 * (M / 32)), 2) void k_decode(DecArgs A, int nt
   }
 
   // ---- state back ----
+  if (AH == 1 || wv < FT) {
 #pragma unroll
-  for (int dt = 0; dt < DV / 32; ++dt)
+    for (int dt = 0; dt < DV / 32; ++dt)
 #pragma unroll
-    for (int vv = 0; vv < 16; ++vv) Ms[(size_t)(wv * 32 + crow(vv, h)) * DV + dt * 32 + col] = Mreg[dt][vv];
-  if (h == 0) as[wv * 32 + col] = areg;
+      for (int vv = 0; vv < 16; ++vv) Ms[(size_t)(wp * 32 + crow(vv, h)) * DV + dt * 32 + col] = Mreg[dt][vv];
+    if (h == 0) as[wp * 32 + col] = areg;
+  }
   if (tid == 0) A.rho[sh] = R;
   // the last min(NTOK, w) tokens into their ring slots
   {
@@ -420,7 +450,7 @@ __global__ __launch_bounds__(256) void k_decode_advance(int64_t* pos, int64_t S,
 template <typename T, int D, int DV, int M, int NA>
 static int run_decode(int64_t S, DecArgs a, int ntok, hipStream_t st) {
   // the caller bounds S*H by max_decode_groups (one workgroup each)
-  static_assert(max_decode_groups(M) * DCfg<T, D, DV, M, NA, 1>::NT < ((int64_t)1 << 32), "decode grid");
+  static_assert(max_decode_groups(M) * DCfg<T, D, DV, M, NA, 8>::NT < ((int64_t)1 << 32), "decode grid");
   (void)hipGetLastError();                             // an earlier call's error is not this one's
   const unsigned groups = (unsigned)(S * a.H);
   if (ntok == 1) {

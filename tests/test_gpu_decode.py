@@ -336,3 +336,20 @@ def test_decode_chunk_non_finite_anchor_leaves_with_the_window(D, m, w, P, T, dt
     assert np.isfinite(got[:, :, clean]).all()
     assert rel_l2(got[:, :, clean], exp[:, :, clean]) < 1e-6
     assert not np.isfinite(got[:, :, ~clean]).all(-1).any()
+
+
+@pytest.mark.parametrize("dtype,D,m,w,P,T", [
+    ("bf16", 32, 32, 128, 0, 70),      # two groups of two tiles; the second has no anchor at first
+    ("bf16", 32, 32, 90, 100, 9),      # three groups
+    ("f32", 64, 32, 40, 30, 12),       # two groups, the second with part of a tile
+    ("f32", 64, 32, 128, 1, 40),       # four groups, empty ones at first
+    ("f32", 32, 32, 65, 64, 20),       # three groups, one offset in the last
+])
+def test_decode_anchor_groups(dtype, D, m, w, P, T):
+    """Workgroups of one feature tile give each group of anchor tiles a wave."""
+    test_decode_chunk_matches_steps_and_forward(dtype, D, m, w, P, T)
+
+
+@pytest.mark.parametrize("D,m,w,P,steps,T", [(32, 32, 128, 5, 3, 4), (32, 32, 96, 0, 2, 3)])
+def test_unused_ring_slots_do_not_matter_in_anchor_groups(D, m, w, P, steps, T):
+    test_unused_ring_slots_do_not_matter(D, m, w, P, steps, T)
