@@ -996,11 +996,15 @@ struct StCfg {
   // Anchor groups: F is linear in the anchors, so below four feature tiles each
   // anchor tile of a row gets a wave of its own per feature tile, with its part
   // of F, and the parts of dchi, dv and GB are added through LDS.  One wave per
-  // feature tile left a workgroup of m <= 64 at one or two waves: a wide window
-  // (w = 100, d = 128, m = 64, 127 KB of LDS) ran half a wave per SIMD, 0.68 ms
-  // at 2 x 8 heads x 3001 tokens, now 0.52; float32 d = m = 64, w = 48, 8 heads
-  // x 1000 tokens 0.18 -> 0.11.
-  static constexpr int AH = NP < 4 ? NA : 1;
+  // feature tile left a workgroup of m <= 64 at one or two waves: float32
+  // d = m = 64, w = 48, 8 heads x 1000 tokens 0.18 -> 0.11 ms.  Every group
+  // repeats the row's work on F, though, and bf16 at m = 64 has a wave per SIMD
+  // without more of them: four tiles in two groups (w = 100, d = 64, 2 x 16 x
+  // 4096 0.60 ms whole, 0.87 in four, 0.55 in two; d = 128 1.81, 1.39, 1.34),
+  // and at d = 64 three tiles whole (w = 80 0.83 in three, 0.49 whole; a single
+  // small head 0.055 and 0.064).
+  static constexpr bool B16 = sizeof(T) == 2;
+  static constexpr int AH = NP == 4 ? 1 : B16 && NP == 2 && NA == 4 ? 2 : B16 && NP == 2 && NA == 3 && D == 64 ? 1 : NA;
   static constexpr int NAW = NA / AH;                // anchor tiles per wave
   static constexpr int NW = NP * AH;
   static constexpr int AW = 32 * NA;                 // anchor offsets i - c per row

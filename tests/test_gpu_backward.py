@@ -105,6 +105,7 @@ def test_backward_edge_lengths(D, m, n, w, dt):
 
 @pytest.mark.parametrize("D,m,w,n,dt", [(128, 64, 96, 400, "bf16"), (128, 64, 128, 433, "bf16"),
                                         (64, 64, 100, 300, "bf16"), (32, 32, 128, 290, "bf16"),
+                                        (64, 64, 80, 310, "bf16"), (32, 32, 70, 131, "bf16"),
                                         (64, 64, 96, 250, "f32"), (32, 64, 128, 333, "f32"),
                                         (128, 64, 128, 40, "bf16")])
 def test_backward_wide_windows(D, m, w, n, dt):
