@@ -253,6 +253,7 @@ def test_decode_chunk_matches_steps_and_forward(dtype, D, m, w, P, T):
     (32, 64, 1000, 64, 2, 1, "f32"),
     (64, 32, 33, 5, 1, 1, "f32"),
     (32, 32, 513, 128, 1, 1, "f32"),
+    (32, 32, 40, 20, 64, 20, "bf16"),     # more heads than half the chip's workgroups: rings after the states
 ])
 def test_prefill_state(D, m, n, w, S, H, dt):
     """The prefilled state of every (sequence, head) against the oracle: M and a
