@@ -131,10 +131,20 @@ def _ptr(t: Optional[torch.Tensor], name: str):
     return t.data_ptr()
 
 
-def _stream():
+try:
     # the raw handle, without the Stream object torch.cuda.current_stream builds
     # (4 us of a 21 us decode step's host time)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    _current_device = torch._C._cuda_getDevice
+    _current_raw_stream = torch._C._cuda_getCurrentRawStream
+except AttributeError:                                # a torch without these entry points
+    _current_device = torch.cuda.current_device
+
+    def _current_raw_stream(device):
+        return torch.cuda.current_stream(device).cuda_stream
+
+
+def _stream():
+    return _current_raw_stream(_current_device())
 
 
 def _expect(pairs):
@@ -162,7 +172,7 @@ def _expect(pairs):
         if not t.is_contiguous():
             raise ValueError(f"{name} must be contiguous")
         ptrs.append(t.data_ptr())
-    if idx != torch._C._cuda_getDevice():
+    if idx != _current_device():
         raise ValueError(f"tensors are on {first.device} but the current device is cuda:{torch.cuda.current_device()}")
     return ptrs
 

@@ -149,6 +149,24 @@ def test_binding_refuses_cpu_tensors():
         L.fwd(x, x, x, x, x, om, 4, workspace=torch.zeros(1 << 16, dtype=torch.uint8))
 
 
+def test_binding_without_the_raw_torch_entry_points():
+    """The binding falls back to torch.cuda's public calls where torch lacks the
+    raw device and stream queries it prefers."""
+    import subprocess
+    import sys
+    code = ("import torch\n"
+            "for nm in ('_cuda_getDevice', '_cuda_getCurrentRawStream'):\n"
+            "    if hasattr(torch._C, nm): delattr(torch._C, nm)\n"
+            "from paper_2608_09307_amd import linsimp as L\n"
+            "torch.cuda.current_device = L._current_device = lambda: 3\n"
+            "class S: cuda_stream = 77\n"
+            "torch.cuda.current_stream = lambda dev: S if dev == 3 else None\n"
+            "assert L._stream() == 77\n")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    res = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stderr
+
+
 def test_feature_bank_argument_errors():
     lib = L.lib()
     vp = ctypes.c_void_p
