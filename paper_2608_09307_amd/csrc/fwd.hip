@@ -912,6 +912,9 @@ static int run_fwd(const Shape& s, FwdArgs a, hipStream_t st) {
   constexpr int NW = 12;
   const int BH = (int)s.BH();
   const int nch = (int)s.nch();
+  // (asked before the first launch: a failing query clears the last error)
+  using R = RCfg<T, D, DV, M, NW, NA>;
+  static const int64_t slots = kernel_slots(k_readout<T, D, DV, M, NW, NA>, 64 * NW);
   {
     int tot = (int)s.H * M * D;
     ProfScope ps("prep_omega", st);
@@ -943,12 +946,10 @@ static int run_fwd(const Shape& s, FwdArgs a, hipStream_t st) {
   { ProfScope ps("keyfeat", st);
   k_keyfeat<T, D, M><<<dim3((nch + 3) / 4, BH), 256, 0, st>>>(a); }
   if (a.out != nullptr) {
-    using R = RCfg<T, D, DV, M, NW, NA>;
     constexpr int NFB = R::NFB;
     // a grid that leaves CUs idle gives each round of a chunk's rows a workgroup
     // of its own (it stages the chunk's window again, beside the others): one
     // float32 head of 256 tokens, 8 chunks, 44 -> 21 us
-    static const int64_t slots = kernel_slots(k_readout<T, D, DV, M, NW, NA>, 64 * NW);
     const int parts = (int64_t)nch * BH * NFB * R::RPW <= slots ? R::RPW : 1;
     { ProfScope ps("fwd_readout", st);
     k_readout<T, D, DV, M, NW, NA><<<dim3(nch, BH, NFB * parts), 64 * NW, 0, st>>>(a); }
