@@ -1236,6 +1236,14 @@ __global__ __launch_bounds__((64 * StCfg<T, D, DV, M, NA>::NW), (StCfg<T, D, DV,
     }
     if (t > 0) fetch(t - 1);
     const int i = s0 + t;
+    // (before the row's products, not between them and their reads: there the
+    // compiler counted the wait for the products along the scaling only, and for
+    // d = 32 the path around it read a product's last registers too early)
+    if (fr != 1.0f) {
+      fpart *= fr;
+#pragma unroll
+      for (int dt = 0; dt < DV / 32; ++dt) Fm[dt] *= fr;
+    }
     wave_lds_sync();
     // logits L[c, p] of the row's anchor tiles (regs <-> anchor c = i - a0 - 32an - crow)
     f32x16 acc[NAW];
@@ -1278,13 +1286,8 @@ __global__ __launch_bounds__((64 * StCfg<T, D, DV, M, NA>::NW), (StCfg<T, D, DV,
         ps = add_elems(pf[an][sp], ps);
       }
     }
-    if (fr != 1.0f) {
-      fpart *= fr;
-#pragma unroll
-      for (int dt = 0; dt < DV / 32; ++dt) Fm[dt] *= fr;
-    }
     fpart += dZ * ps;
-    // F <- 2^(R_t - R_{t+1}) F + (sum_c psi_c u_c^T) diag(dN)
+    // F += (sum_c psi_c u_c^T) diag(dN)
 #pragma unroll
     for (int dt = 0; dt < DV / 32; ++dt) {
       f32x16 y = zero16();

@@ -80,6 +80,7 @@ def _run(wl: Workload, pairs=None):
     (64, 64, 333, 64, 1, 1),      # several query-sweep segments, ragged tail
     (32, 64, 70, 1, 2, 1),        # w = 1
     (64, 32, 47, 64, 1, 1),       # a chunk and a half
+    (32, 32, 100, 32, 1, 2),      # every register of the anchor tile in the window
 ])
 def test_backward_f32_structure(D, m, n, w, B, H):
     _run(Workload("f32_bwd", B, H, n, D, D, m, w, "f32", "fwdbwd", seed=31))
