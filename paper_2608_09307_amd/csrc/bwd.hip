@@ -998,13 +998,12 @@ struct StCfg {
   // of F, and the parts of dchi, dv and GB are added through LDS.  One wave per
   // feature tile left a workgroup of m <= 64 at one or two waves: float32
   // d = m = 64, w = 48, 8 heads x 1000 tokens 0.18 -> 0.11 ms.  Every group
-  // repeats the row's work on F, though, and bf16 at m = 64 has a wave per SIMD
-  // without more of them: four tiles in two groups (w = 100, d = 64, 2 x 16 x
-  // 4096 0.60 ms whole, 0.87 in four, 0.55 in two; d = 128 1.81, 1.39, 1.34),
-  // and at d = 64 three tiles whole (w = 80 0.83 in three, 0.49 whole; a single
-  // small head 0.055 and 0.064).
-  static constexpr bool B16 = sizeof(T) == 2;
-  static constexpr int AH = NP == 4 ? 1 : B16 && NP == 2 && NA == 4 ? 2 : B16 && NP == 2 && NA == 3 && D == 64 ? 1 : NA;
+  // repeats the row's work on F, though, and in bf16 at d = m = 64 that outweighs
+  // the waves above two tiles: four of them in two groups (w = 100, 2 x 16 x 4096
+  // 0.60 ms whole, 0.87 in four, 0.55 in two), three whole (w = 80 0.83 in three,
+  // 0.49 whole; a single small head 0.055 and 0.064).
+  static constexpr bool SMALL = sizeof(T) == 2 && D == 64 && NP == 2;
+  static constexpr int AH = NP == 4 ? 1 : SMALL && NA == 4 ? 2 : SMALL && NA == 3 ? 1 : NA;
   static constexpr int NAW = NA / AH;                // anchor tiles per wave
   static constexpr int NW = NP * AH;
   static constexpr int AW = 32 * NA;                 // anchor offsets i - c per row
@@ -1222,6 +1221,14 @@ __global__ __launch_bounds__((64 * StCfg<T, D, DV, M, NA>::NW), (StCfg<T, D, DV,
     const float inv = uniform(invn);
     const float dZ = uniform(dZn);
     const float fr = uniform(t < tlast ? fast_exp2(sRj[t] - sRj[t + 1]) : cb < cbl ? fast_exp2(sRj[t] - Rnext) : 1.0f);
+    // (before the row's products, not between them and their reads: there the
+    // compiler counted the wait for the products along the scaling only, and for
+    // d = 32 the path around it read a product's last registers too early)
+    if (fr != 1.0f) {
+      fpart *= fr;
+#pragma unroll
+      for (int dt = 0; dt < DV / 32; ++dt) Fm[dt] *= fr;
+    }
 #pragma unroll
     for (int e = 0; e < QE; ++e)
       if (e * 64 + l < D) {
@@ -1236,14 +1243,6 @@ __global__ __launch_bounds__((64 * StCfg<T, D, DV, M, NA>::NW), (StCfg<T, D, DV,
     }
     if (t > 0) fetch(t - 1);
     const int i = s0 + t;
-    // (before the row's products, not between them and their reads: there the
-    // compiler counted the wait for the products along the scaling only, and for
-    // d = 32 the path around it read a product's last registers too early)
-    if (fr != 1.0f) {
-      fpart *= fr;
-#pragma unroll
-      for (int dt = 0; dt < DV / 32; ++dt) Fm[dt] *= fr;
-    }
     wave_lds_sync();
     // logits L[c, p] of the row's anchor tiles (regs <-> anchor c = i - a0 - 32an - crow)
     f32x16 acc[NAW];
