@@ -76,7 +76,10 @@ def test_case_against_64_bits(case):
         err = np.sqrt(((heads - ref) ** 2).sum(axes)) / np.maximum(np.sqrt((ref ** 2).sum(axes)), 1e-30)
         rows = None
         if g.ndim == 4 and nm != "dk":
-            rows = row_max_rel(heads, ref)
+            # (dq of a sequence's first row is zero by definition: what is there is the
+            # rounding of the bf16 output its two terms were formed from)
+            first = 1 if nm == "dq" else 0
+            rows = row_max_rel(heads[:, first:], ref[:, first:])
         print(f"      {nm} head {err.max():.2e}" + (f" row {rows:.2e}" if rows is not None else ""), flush=True)
         assert err.max() <= tol, (nm, err.max())
         assert rows is None or rows <= row_tol, (nm, "row", rows)
