@@ -33,8 +33,9 @@ FLAGS = [
 ]
 
 # Per-source additions.  The backward's machine scheduler tracks register
-# pressure with the target's own trackers: the dq/dr sweep spills 60 instead
-# of 75 registers at its 256 and runs 3-4% faster (elsewhere the option raised
+# pressure with the target's own trackers: when it was added the dq/dr sweep
+# spilled 60 instead of 75 registers at its 256 and ran 3-4% faster (today's
+# spills 24 at d = m = 128 with it and without; elsewhere the option raised
 # register counts and lowered occupancy, so it stays local).
 SOURCE_FLAGS = {"bwd.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers"]}
 

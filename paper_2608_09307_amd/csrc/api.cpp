@@ -233,7 +233,7 @@ static int check_dims(const linsimp_dims* d, Shape* s, bool backward, bool bh_on
 }
 
 // the decode kernel runs one workgroup per (sequence, head) on a one-dimensional
-// grid, whose thread count must stay below 2^32
+// grid of fewer than 2^32 threads
 static int check_decode_grid(int64_t S, int32_t H, int32_t m) {
   const int64_t most = max_decode_groups(m);
   if (S * (int64_t)H > most) {

@@ -54,7 +54,7 @@ struct DecArgs {
 // VALU instructions and 32 matrix products each).  A form that met at five
 // barriers per token (key frame, row shift, sums), formed z = q (*) r in every
 // wave and read the bank from L2 for each token took 161 us for 16 tokens of
-// 32 sequences x 16 heads (d = m = 128, w = 64), this one 89.  A single step
+// 32 sequences x 16 heads (d = m = 128, w = 64), this one 86.  A single step
 // moves each state element once: 256 x 16 at d = m = 128 0.145 ms, 4.8 TB/s,
 // the rate of a copy.
 // ---------------------------------------------------------------------------

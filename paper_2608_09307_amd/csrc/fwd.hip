@@ -770,7 +770,7 @@ __global__ __launch_bounds__(64 * NW) void k_readout(FwdArgs a) {
       // per 32-wide slice of d: boundary readout + correction, then the anchor
       // combine N += A_c (*) u_c  (lanes <-> d, regs <-> anchor)
       // (unrolled up to two slices; four would spill 47 of the 168 registers that
-      // three waves per SIMD leave)
+      // three waves per SIMD leave; float32 d = m = 64 spills 12 to 14 with two)
       constexpr int kUnroll = DV / 32 <= 2 ? DV / 32 : 1;
 #pragma unroll kUnroll
       for (int dt = 0; dt < DV / 32; ++dt) {
